@@ -191,19 +191,19 @@ int mc_build_network(const mc_config* cfg, mc_net** out);
  * getters synchronize.  Resumable: consecutive calls continue the same
  * trajectory bit for bit.  Errors: STATE (host-only or failed handle), HIP,
  * OOM (raster growth).  Test hook: the environment variable
- * MC_PERSIST_LIST_CAP = k (1..1024) makes the persistent scheme, in the
- * steps that mc_profile_phases runs, list every step of more than k spikes
- * in producer order after the wait (the path of a step beyond its LDS
- * list); results are unchanged. */
+ * MC_PERSIST_LIST_CAP = k makes the persistent scheme, in the steps that
+ * mc_profile_phases runs, hold at most k spike ids (but always a workgroup's
+ * own targets) in its LDS queue, so that its poller has to wait for room;
+ * results are unchanged. */
 int mc_simulate(mc_net* net, int64_t steps);
 
 /* For callers that cannot allocate memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation): mc_simulate for the
  * persistent scheme (mc_set_launch scheme 1) without any allocation -- no
  * hipMalloc or hipFree, no graph instantiation, no raster drain.  The
- * kernels' spike records and side array (the scratch mc_simulate keeps in
+ * kernels' spike records (the scratch mc_simulate keeps in
  * library-allocated memory) come from a file-scope device array of about
- * 4.1 MiB (room for 512 workgroups of 512 targets) that each GPU holds until
+ * 0.25 MiB (room for 512 workgroups of 512 targets) that each GPU holds until
  * the process ends.  The records are cleared by a kernel at the start of
  * every call.  Every call on one GPU shares that GPU's array, so calls that
  * overlap on one GPU (two networks on concurrent streams) race: serialize
@@ -307,16 +307,16 @@ int mc_get_persist_shape(mc_net* net, int32_t* workgroups_out, int32_t* targets_
  * deliver, communicate and other): simulates `steps` steps with per-phase
  * device timestamps (persistent schemes only) and returns the mean time per
  * step in microseconds, averaged
- * over workgroups: us_out[0] update, [1] compaction+publication, [2] wait
- * for every workgroup's spikes, [3] spike-list gather, [4] delivery (LDS
- * window: the delay-1 events; buckets: every event of the step), [5] the
- * sum of [0..4]; overlapping parts of [2]: [6] drive of the next step (and,
- * in the LDS window, pending delivery of the previous one; first
- * wavefront), [7] polling (first polling thread).  The trajectory is the
- * one mc_simulate would produce. */
+ * over workgroups, of the first wavefront (buckets: thread): us_out[0] update,
+ * [1] compaction+publication, [2] wait for spikes and their delivery, [3]
+ * spike-list gather (LDS window: 0, listing is the poller's work), [4]
+ * delivery by this wavefront, [5] the sum of [0..4]; besides these: [6] drive
+ * of the next steps (buckets: overlaps [2]), [7] polling (first polling
+ * thread; overlaps the others).  The trajectory is the one mc_simulate would
+ * produce. */
 int mc_profile_phases(mc_net* net, int64_t steps, double* us_out_host);
 /* The per-workgroup times behind the last mc_profile_phases, [G][8] us per
- * step (columns 0..4 as us_out[0..4], 5: drive + pending delivery of
+ * step (columns 0..4 as us_out[0..4], 5: drive of
  * wavefront 0, 6: polling of the first poller, 7: unused); *workgroups_out =
  * G (0 before any profile).  BUFFER_TOO_SMALL if capacity < 8*G. */
 int mc_get_phase_table(mc_net* net, double* out_host, int64_t capacity, int32_t* workgroups_out);

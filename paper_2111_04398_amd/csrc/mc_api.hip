@@ -146,8 +146,8 @@ struct mc_net {
   int wall_khz = 100000;               // wall_clock64 rate (kHz)
   int lds_max = 65536;
   int pG = 0, pB = 0, pDL = 0;
+  int plsh = 0;                        // log2 of the lanes per spike of a delivery
   int horizon = kRingSlots - 1;        // ring slots ahead of the current step that may hold input
-  long long* d_blk = nullptr;
   unsigned long long* d_flags = nullptr;
   unsigned long long* d_bk = nullptr;  // bucket scheme: [G][128][bk_cap] entries
   int bk_cap = 0;
@@ -177,8 +177,8 @@ struct mc_net {
   unsigned long long* d_phase = nullptr;
   bool phase_on = false;
   std::vector<double> phase_wg;        // per-workgroup phase times (us/step) of the last mc_profile_phases
-  unsigned* d_nb = nullptr;            // near table offsets [n_pad][pG+1]
-  unsigned long long* d_ne = nullptr;  // near table entries
+  unsigned* d_off = nullptr;           // packed rows: sub-row bounds [n_pad][pG+1]
+  unsigned long long* d_pk = nullptr;  // and entries [M]
   // recording
   int n_wg = 0;
   int qpw = 0;
@@ -263,10 +263,9 @@ struct mc_net {
     a.G = pG; a.B = pB; a.DL = pDL; a.BW = (pB + 31) / 32;
     a.horizon = horizon;
     a.bstart = d_bstart;
-    a.blk = d_blk; a.flags = d_flags; a.pub = d_pub;
+    a.off = d_off; a.pk = d_pk; a.lsh = plsh; a.flags = d_flags;
     a.wait_ticks = (long long)wall_khz * 1000 * kWaitSeconds;
     a.phase = phase_on ? d_phase : nullptr;
-    a.nb = d_nb; a.ne = d_ne;
     if (const char* lc = getenv("MC_PERSIST_LIST_CAP")) a.list_cap = std::max(0, atoi(lc));
     return a;
   }
@@ -303,9 +302,8 @@ int release_recording(mc_net* n) {
 void release_all(mc_net* n) {
   if (n->graph) { (void)hipGraphExecDestroy(n->graph); n->graph = nullptr; }
   release_recording(n);
-  dev_free(n->alloc, n->d_blk); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_pub); dev_free(n->alloc, n->d_phase);
-  dev_free(n->alloc, n->d_nb); dev_free(n->alloc, n->d_bk);
-  dev_free(n->alloc, n->d_ne);
+  dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_pub); dev_free(n->alloc, n->d_phase);
+  dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_pk); dev_free(n->alloc, n->d_bk);
   dev_free(n->alloc, n->d_bstart);
   dev_free(n->alloc, n->d_qinst); dev_free(n->alloc, n->d_inst_base); dev_free(n->alloc, n->d_ilist); dev_free(n->alloc, n->d_icnt);
   dev_free(n->alloc, n->d_bt0); dev_free(n->alloc, n->d_binst); dev_free(n->alloc, n->d_blb); dev_free(n->alloc, n->d_ifb); dev_free(n->alloc, n->d_boff);
@@ -495,7 +493,8 @@ int validate_launch(const mc_net* n, const mc_launch& l) {
 
 // Shape of the persistent scheme: G co-resident workgroups, workgroup g owning
 // targets [bs[g], bs[g+1]) (B of them, the last block possibly fewer), DL
-// near steps of input in LDS (as many as the LDS holds, <= 101).
+// steps of pending input in LDS (as many as the LDS holds; delays up to DL-2
+// go there, so 102 cover them all).
 // neurons_per_wg = 0: one workgroup per compute unit.  (Blocks sized to
 // equalise the expected synaptic input per workgroup were measured slower on
 // the full microcircuit: the larger blocks leave fewer delay steps in LDS.)
@@ -520,7 +519,7 @@ int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, std::v
   const int per_cu = (g + n->n_cu - 1) / n->n_cu;
   const size_t budget = (size_t)n->lds_max / per_cu;
   if (stat + base + 2 * (size_t)b * 8 > budget) return set_error(MC_ERR_RANGE, "LDS too small for the persistent scheme");
-  const int dl = (int)std::min<size_t>(101, (budget - stat - base) / ((size_t)b * 8));
+  const int dl = (int)std::min<size_t>(102, (budget - stat - base) / ((size_t)b * 8));
   const size_t lds = persist_lds_bytes(g, b, dl);
   HIP_TRY(persist_set_lds_limit(lds));
   int occ = 0;
@@ -685,32 +684,20 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     if ((rc = fold_counters(n)) != MC_OK) return rc;
     release_recording(n);   // sized for the old shape
     if (l.scheme == MC_SCHEME_PERSISTENT_LDS) {
-      dev_free(n->alloc, n->d_blk); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_pub); dev_free(n->alloc, n->d_bstart);
-      if ((rc = dev_alloc(n->alloc, &n->d_blk, (size_t)n->n_pad * (G + 1))) != MC_OK) return rc;
-      if ((rc = dev_alloc(n->alloc, &n->d_flags, persist_flag_words(G))) != MC_OK) return rc;
-      if ((rc = dev_alloc(n->alloc, &n->d_pub, (size_t)G * kRecSlots * B)) != MC_OK) return rc;
+      dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_pk); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_bstart);
+      if ((rc = dev_alloc(n->alloc, &n->d_off, (size_t)n->n_pad * (G + 1))) != MC_OK) return rc;
+      if ((rc = dev_alloc(n->alloc, &n->d_pk, (size_t)n->h.M)) != MC_OK) return rc;
+      if ((rc = dev_alloc(n->alloc, &n->d_flags, window_flag_words(G))) != MC_OK) return rc;
       if ((rc = dev_alloc(n->alloc, &n->d_bstart, (size_t)G + 1)) != MC_OK) return rc;
       HIP_TRY(hipMemcpy(n->d_bstart, bs.data(), sizeof(int) * (G + 1), hipMemcpyHostToDevice));
       n->bstart_host = bs;
-      HIP_TRY(launch_build_blk(n->d_row_ptr, n->d_tgt, n->n_pad, G, n->d_bstart, n->d_blk, n->stream));
-      HIP_TRY(hipMemsetAsync(n->d_flags, 0, sizeof(unsigned long long) * persist_flag_words(G), n->stream));
-      // near table: the delay-1/2 synapses per (source, workgroup), CSR
-      dev_free(n->alloc, n->d_nb); dev_free(n->alloc, n->d_ne);
-      const size_t cells = (size_t)n->n_pad * (G + 1);
-      if ((rc = dev_alloc(n->alloc, &n->d_nb, cells)) != MC_OK) return rc;
-      HIP_TRY(launch_near_count(n->d_tgt, n->d_dly, n->d_blk, n->n_pad, G, n->d_nb, n->stream));
-      std::vector<unsigned> hc;
-      try { hc.resize(cells); } catch (...) { return set_error(MC_ERR_OOM, "host allocation of the near-table offsets failed"); }
+      HIP_TRY(hipMemsetAsync(n->d_flags, 0, sizeof(unsigned long long) * window_flag_words(G), n->stream));
+      HIP_TRY(launch_pack_rows(n->d_row_ptr, n->d_tgt, n->d_wq, n->d_dly, n->n_pad, G, B, n->d_off, n->d_pk, n->stream));
       HIP_TRY(hipStreamSynchronize(n->stream));
-      HIP_TRY(hipMemcpy(hc.data(), n->d_nb, sizeof(unsigned) * cells, hipMemcpyDeviceToHost));
-      uint64_t total = 0;
-      for (size_t k = 0; k < cells; ++k) { const unsigned c = hc[k]; hc[k] = (unsigned)total; total += c; }
-      if (total >= ((uint64_t)1 << 32)) return set_error(MC_ERR_RANGE, "more than 2^32 delay-1/2 synapses");
-      HIP_TRY(hipMemcpy(n->d_nb, hc.data(), sizeof(unsigned) * cells, hipMemcpyHostToDevice));
-      if ((rc = dev_alloc(n->alloc, &n->d_ne, (size_t)std::max<uint64_t>(total, 1))) != MC_OK) return rc;
-      HIP_TRY(launch_near_fill(n->d_tgt, n->d_wq, n->d_dly, n->d_blk, n->d_bstart, n->n_pad, G, n->d_nb, n->d_ne,
-                               n->stream));
-      HIP_TRY(hipStreamSynchronize(n->stream));
+      // lanes per spike: the power of two that covers a mean sub-row
+      const double mean = (double)n->h.M / ((double)std::max<int64_t>(1, n->h.N) * G);
+      n->plsh = 2;
+      while (n->plsh < 5 && (double)(1 << n->plsh) < mean) ++n->plsh;
     }
     if (l.scheme == MC_SCHEME_TARGET_OWNER &&
         (rc = setup_owner(n, l.neurons_per_wg ? l.neurons_per_wg : 256, kOwnerMaxTargets)) != MC_OK)
@@ -1092,17 +1079,15 @@ int mc_simulate_noalloc(mc_net* n, int64_t steps) {
   HIP_TRY(hipGetDevice(&cur));
   if (cur != n->device) return set_error(MC_ERR_INVALID_ARG, "the network's device is not the current device");
   unsigned long long* rec = nullptr;
-  int* pub = nullptr;
-  HIP_TRY(noalloc_scratch(n->device, &rec, &pub));
+  HIP_TRY(noalloc_scratch(n->device, &rec));
   HIP_TRY(hipEventRecord(n->ev0, n->stream));
   n->launches_timed = 0;
   n->steps_timed = 0;
   n->whole_call = false;
-  HIP_TRY(launch_clear_records(rec, persist_flag_words(n->pG), n->stream));
+  HIP_TRY(launch_clear_records(rec, window_flag_words(n->pG), n->stream));
   const DevNet p = n->dev();
   PersistArgs a = n->persist();
   a.flags = rec;
-  a.pub = pub;
   int rc;
   for (int64_t left = steps; left > 0;) {
     const int chunk = (int)std::min<int64_t>(left, 1 << 20);
@@ -1306,8 +1291,7 @@ int mc_stream(mc_net* n, void** s) {
 
 // Replaces every weight (mode 0: from pA values; 1/2: one gradient step):
 // a check pass first, so that a rejected update leaves the store unchanged;
-// then the store, the persistent scheme's near-table copies of the delay-1/2
-// weights and the host copy.
+// then the store, the persistent scheme's packed rows and the host copy.
 static int update_weights(mc_net* n, const void* src, int mode, double eta) {
   HIP_TRY(hipMemsetAsync(n->d_wbad, 0, sizeof(unsigned), n->stream));
   HIP_TRY(launch_weights(n->d_wq, src, mode, eta, n->h.M, n->d_wbad, true, n->stream));
@@ -1317,9 +1301,8 @@ static int update_weights(mc_net* n, const void* src, int mode, double eta) {
   if (bad) return set_error(MC_ERR_RANGE, "a new weight is not finite or does not fit int32 in units of 2^-16 pA "
                                           "(|w| < 32768 pA); the store is unchanged");
   HIP_TRY(launch_weights(n->d_wq, src, mode, eta, n->h.M, n->d_wbad, false, n->stream));
-  if (n->launch.scheme == MC_SCHEME_PERSISTENT_LDS && n->pG > 0 && n->d_ne)
-    // the near table holds copies of the delay-1/2 weights
-    HIP_TRY(launch_near_fill(n->d_tgt, n->d_wq, n->d_dly, n->d_blk, n->d_bstart, n->n_pad, n->pG, n->d_nb, n->d_ne,
+  if (n->launch.scheme == MC_SCHEME_PERSISTENT_LDS && n->pG > 0 && n->d_pk)   // the packed rows hold copies of the weights
+    HIP_TRY(launch_pack_rows(n->d_row_ptr, n->d_tgt, n->d_wq, n->d_dly, n->n_pad, n->pG, n->pB, n->d_off, n->d_pk,
                              n->stream));
   HIP_TRY(hipStreamSynchronize(n->stream));
   HIP_TRY(hipMemcpy(n->h.wq.data(), n->d_wq, sizeof(int32_t) * n->h.M, hipMemcpyDeviceToHost));
@@ -1618,11 +1601,11 @@ int mc_probe_exchange(mc_net* n, int64_t steps, double* us) {
   if (steps < 1 || steps > 10000000) return set_error(MC_ERR_INVALID_ARG, "steps out of [1, 1e7]");
   unsigned long long* flags = nullptr;
   unsigned* err_word = nullptr;
-  int rc = dev_alloc(n->alloc, &flags, persist_flag_words(n->pG));
+  int rc = dev_alloc(n->alloc, &flags, window_flag_words(n->pG));
   if (rc != MC_OK) return rc;
   if ((rc = dev_alloc(n->alloc, &err_word, 1)) != MC_OK) { dev_free(n->alloc, flags); return rc; }
   const long long wait = (long long)n->wall_khz * 1000 * kWaitSeconds;
-  hipError_t err = hipMemsetAsync(flags, 0, sizeof(unsigned long long) * persist_flag_words(n->pG), n->stream);
+  hipError_t err = hipMemsetAsync(flags, 0, sizeof(unsigned long long) * window_flag_words(n->pG), n->stream);
   if (err == hipSuccess) err = hipMemsetAsync(err_word, 0, sizeof(unsigned), n->stream);
   if (err == hipSuccess) err = launch_exchange_probe(flags, n->pG, n->launch.block, std::min<int64_t>(steps, 1000), wait, err_word, n->stream);
   if (err == hipSuccess) err = hipEventRecord(n->ev0, n->stream);

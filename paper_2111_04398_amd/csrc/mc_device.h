@@ -76,53 +76,45 @@ struct PersistArgs {
   int G;                       // workgroups (all co-resident, G <= 2 * block, G <= 512)
   int B;                       // most target neurons of one workgroup (multiple of 4, <= kPersistMaxB)
   const int* bstart;           // [G+1] workgroup g owns padded targets [bstart[g], bstart[g+1]) (multiples of 4)
-  int DL;                      // near slots held in LDS (2..101)
+  int DL;                      // steps of pending input held in LDS (2..102)
   int horizon;                 // ring slots ahead of the first step that may hold input at launch (<= 127)
   int BW;                      // 32-bit words per far-bitmap row: ceil(B/32)
-  const long long* blk;        // [n_pad][G+1] first synapse of each row with target >= bstart[g]
-  unsigned long long* flags;   // [G][kRecSlots][8] spike records by step mod kRecSlots, then the
+  // packed rows (see k_pack_rows): row i's entries at row_ptr[i] + off[i][q]
+  // .. off[i][q+1] are those of the workgroup at place q when the workgroups
+  // are ordered by XCD (g mod 8, then g)
+  const unsigned* off;         // [n_pad][G+1]
+  const unsigned long long* pk;   // [M] delay << 48 | local target << 32 | weight
+  int lsh;                     // log2 of the lanes that share one spike's entries in a delivery (0..6)
+  unsigned long long* flags;   // [kRecSlots][G][kWinRecWords] spike records by step mod kRecSlots, then the
                                // launch's finish counter (one word, zero between launches)
-  int* pub;                    // [G][kRecSlots][B] published spike ids beyond the seventh
   long long wait_ticks;        // longest wait for one step's records, in wall_clock64 ticks (then: error bit 2)
   unsigned long long* phase;   // optional [G*8]: summed wall_clock64 ticks per phase (nullptr: off)
-  // near table: the delay-1/2 synapses of row i into workgroup g's block are
-  // ne[nb[i][p] .. nb[i][p+1]) with p the position of g when the workgroups
-  // are ordered by XCD (g mod 8, then g), each (target - bstart[g]) << 32 |
-  // weight, bit 31 of the target field set for delay 2
-  const unsigned* nb;          // [n_pad][G+1]
-  const unsigned long long* ne;
-  // spikes of a step above which it is listed in producer order after the
-  // wait (0: the LDS list's capacity); a smaller value is a test hook that
-  // sends ordinary steps down that path (phase-timing instance only)
+  // ids the queue holds at most (0: its capacity); a smaller value is a test
+  // hook that makes the poller wait for room (phase-timing instance only)
   int list_cap;
 };
 constexpr int kPersistFlagStride = 8;
 constexpr int kRecSlots = 4;            // spike records (and side arrays) per workgroup, by step mod 4
 __host__ __device__ inline size_t persist_record_words(int G) { return (size_t)G * kRecSlots * kPersistFlagStride; }
 __host__ __device__ inline size_t persist_flag_words(int G) { return persist_record_words(G) + kPersistFlagStride; }
+constexpr int kWinRecWords = 16;        // words of a spike record of the LDS-window scheme (one 128-byte line)
+__host__ __device__ inline size_t window_record_words(int G) { return (size_t)G * kRecSlots * kWinRecWords; }
+__host__ __device__ inline size_t window_flag_words(int G) { return window_record_words(G) + kPersistFlagStride; }
 constexpr int kPersistMaxB = 512;       // owned targets per workgroup (one per thread)
 constexpr int kPersistMaxBlock = 512;   // threads per workgroup: 256 VGPRs per lane, no scratch spills
 size_t persist_lds_bytes(int G, int B, int DL);
-// Near table: counts per (source, workgroup), then (after an exclusive scan)
-// the fill.
-hipError_t launch_near_count(const int32_t* tgt, const uint8_t* dly, const long long* blk, long long n_pad, int G,
-                             unsigned* cnt, hipStream_t s);
-hipError_t launch_near_fill(const int32_t* tgt, const int32_t* wq, const uint8_t* dly, const long long* blk,
-                            const int* bstart, long long n_pad, int G, const unsigned* nb, unsigned long long* ne,
-                            hipStream_t s);
+// Fills the packed rows and their sub-row bounds for G workgroups of B targets.
+hipError_t launch_pack_rows(const int64_t* row_ptr, const int32_t* tgt, const int32_t* wq, const uint8_t* dly,
+                            long long n_pad, int G, int B, unsigned* off, unsigned long long* pk, hipStream_t s);
 hipError_t persist_static_lds(size_t* bytes);
 hipError_t persist_occupancy(int block, size_t lds, int* blocks_per_cu);
 hipError_t persist_set_lds_limit(size_t lds);
 hipError_t launch_persist(const DevNet& p, const PersistArgs& a, int steps, int block, hipStream_t s);
-// Scratch of the allocation-free entry point (mc_noalloc.hip): spike records
-// (noalloc_record_words() words, room for 512 workgroups) and the side array
-// (512 x kRecSlots x 512 ints) of this device; and a record clear by kernel.
-size_t noalloc_scratch_bytes();
+// Scratch of the allocation-free entry point (mc_noalloc.hip): the spike
+// records of this device (room for 512 workgroups); and a record clear by kernel.
 size_t noalloc_record_words();
-hipError_t noalloc_scratch(int device, unsigned long long** records, int** pub);
+hipError_t noalloc_scratch(int device, unsigned long long** records);
 hipError_t launch_clear_records(unsigned long long* records, size_t words, hipStream_t s);
-hipError_t launch_build_blk(const int64_t* row_ptr, const int32_t* tgt, long long n_pad, int G, const int* bstart,
-                            long long* blk, hipStream_t s);
 
 constexpr int kReplayChunkHost = 256;     // must equal the replay kernel's chunk
 hipError_t launch_replay(const int2* spikes, const long long* first_item, int n_spikes, long long n_items,
@@ -135,7 +127,7 @@ hipError_t launch_atomic_slots(unsigned long long* table, long long slots, long 
                                hipStream_t s);
 // Empty persistent loop of G co-resident workgroups exchanging one spike
 // record per step (no neurons, no delivery): the exchange's latency floor.
-// flags: persist_flag_words(G) words, zero on entry and on exit.
+// flags: window_flag_words(G) words, zero on entry and on exit.
 hipError_t launch_exchange_probe(unsigned long long* flags, int G, int block, long long steps, long long wait_ticks,
                                  unsigned* err, hipStream_t s);
 

@@ -1,11 +1,10 @@
 // mc_noalloc.hip -- device scratch of the allocation-free simulation entry
 // point (mc_simulate_noalloc).
 //
-// The persistent kernel exchanges spikes through per-workgroup records and a
-// side array for the ids beyond those a record carries.  mc_simulate keeps
-// them in memory the library allocates when the launch shape is set; the
-// allocation-free entry point takes them from this file-scope array instead,
-// sized for the largest persistent shape (512 workgroups of 512 targets).
+// The persistent kernel exchanges spikes through per-workgroup records.
+// mc_simulate keeps them in memory the library allocates when the launch shape
+// is set; the allocation-free entry point takes them from this file-scope
+// array instead, sized for the largest persistent shape (512 workgroups).
 // Every GPU the library runs on holds its own copy until the process ends.
 // Host code must not pass `scratch` itself to a kernel (on the host it is a
 // stand-in symbol, not a device address): the device address is looked up
@@ -18,11 +17,9 @@ namespace mc {
 
 namespace {
 
-constexpr size_t kScratchRecordWords = (size_t)kPersistMaxBlock * kRecSlots * kPersistFlagStride + kPersistFlagStride;
-constexpr size_t kScratchPubInts = (size_t)kPersistMaxBlock * kRecSlots * kPersistMaxB;
-constexpr size_t kScratchWords = kScratchRecordWords + kScratchPubInts / 2;
+constexpr size_t kScratchRecordWords = (size_t)kPersistMaxBlock * kRecSlots * kWinRecWords + kPersistFlagStride;
 
-static __device__ __align__(256) unsigned long long scratch[kScratchWords];
+static __device__ __align__(256) unsigned long long scratch[kScratchRecordWords];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -35,13 +32,11 @@ __global__ void k_fill_u64(unsigned long long* p, long long n, unsigned long lon
 
 }  // namespace
 
-size_t noalloc_scratch_bytes() { return sizeof(unsigned long long) * kScratchWords; }
 size_t noalloc_record_words() { return kScratchRecordWords; }
 
 // Device address of this device's scratch, looked up on the first call for
-// the device (which must be current) and kept: records first, then the side
-// array of ids.
-hipError_t noalloc_scratch(int device, unsigned long long** records, int** pub) {
+// the device (which must be current) and kept.
+hipError_t noalloc_scratch(int device, unsigned long long** records) {
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(g_scratch_mutex);
   if (!g_scratch_ptr[device]) {
@@ -56,7 +51,6 @@ hipError_t noalloc_scratch(int device, unsigned long long** records, int** pub) 
     g_scratch_ptr[device] = ptr;
   }
   *records = static_cast<unsigned long long*>(g_scratch_ptr[device]);
-  *pub = reinterpret_cast<int*>(*records + kScratchRecordWords);
   return hipSuccess;
 }
 
