@@ -83,9 +83,9 @@ struct PersistArgs {
   // .. off[i][q+1] are those of the workgroup at place q when the workgroups
   // are ordered by XCD (g mod 8, then g)
   const unsigned* off;         // [n_pad][G+1]
-  const unsigned long long* pk;   // [M] delay << 48 | local target << 32 | weight
+  const unsigned long long* pk;   // [M] (delay * B + local target) * 8 << 32 | weight
   int lsh;                     // log2 of the lanes that share one spike's entries in a delivery (0..6)
-  unsigned long long* flags;   // [kRecSlots][G][kWinRecWords] spike records by step mod kRecSlots, then the
+  unsigned long long* flags;   // spike records by step mod kRecSlots (window_word0, window_map), then the
                                // launch's finish counter (one word, zero between launches)
   long long wait_ticks;        // longest wait for one step's records, in wall_clock64 ticks (then: error bit 2)
   unsigned long long* phase;   // optional [G*8]: summed wall_clock64 ticks per phase (nullptr: off)
@@ -97,8 +97,19 @@ constexpr int kPersistFlagStride = 8;
 constexpr int kRecSlots = 4;            // spike records (and side arrays) per workgroup, by step mod 4
 __host__ __device__ inline size_t persist_record_words(int G) { return (size_t)G * kRecSlots * kPersistFlagStride; }
 __host__ __device__ inline size_t persist_flag_words(int G) { return persist_record_words(G) + kPersistFlagStride; }
-constexpr int kWinRecWords = 16;        // words of a spike record of the LDS-window scheme (one 128-byte line)
-__host__ __device__ inline size_t window_record_words(int G) { return (size_t)G * kRecSlots * kWinRecWords; }
+// Spike records of the LDS-window scheme: word 0 of every workgroup's record
+// of a step side by side (a poll of 64 of them reads four lines), then the
+// bitmap words (a line per record).
+constexpr int kWinMapWords = 16;
+#ifndef W0STRIDE
+#define W0STRIDE 4
+#endif
+constexpr int kWord0Stride = W0STRIDE;
+__host__ __device__ inline size_t window_word0(int G, int slot, int g) { return ((size_t)slot * ((G + 15) / 16 * 16) + g) * kWord0Stride; }
+__host__ __device__ inline size_t window_map(int G, int slot, int g) {
+  return window_word0(G, kRecSlots, 0) + ((size_t)slot * G + g) * kWinMapWords;
+}
+__host__ __device__ inline size_t window_record_words(int G) { return window_map(G, kRecSlots, 0); }
 __host__ __device__ inline size_t window_flag_words(int G) { return window_record_words(G) + kPersistFlagStride; }
 constexpr int kPersistMaxB = 512;       // owned targets per workgroup (one per thread)
 constexpr int kPersistMaxBlock = 512;   // threads per workgroup: 256 VGPRs per lane, no scratch spills

@@ -17,7 +17,7 @@ namespace mc {
 
 namespace {
 
-constexpr size_t kScratchRecordWords = (size_t)kPersistMaxBlock * kRecSlots * kWinRecWords + kPersistFlagStride;
+constexpr size_t kScratchRecordWords = (size_t)kPersistMaxBlock * kRecSlots * (kWord0Stride + kWinMapWords) + kPersistFlagStride;
 
 static __device__ __align__(256) unsigned long long scratch[kScratchRecordWords];
 

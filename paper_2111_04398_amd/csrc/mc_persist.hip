@@ -14,8 +14,8 @@
 //
 // Packed rows.  Delivery reads a copy of the store made for this launch shape:
 // every row keeps its place (row_ptr) but is reordered by target workgroup,
-// the workgroups in XCD order, one 8-byte word per synapse (delay, local
-// target, weight), with the sub-row bounds of every (row, workgroup) in `off`.
+// the workgroups in XCD order, one 8-byte word per synapse (weight, and the
+// delay and local target as one offset into the LDS window), with the sub-row bounds of every (row, workgroup) in `off`.
 // One load per synapse instead of three, and the 32 workgroups of an XCD read
 // adjacent parts of a row, so that cache lines are shared inside one L2.
 //
@@ -65,6 +65,7 @@
 #pragma clang fp contract(off)
 
 #include <algorithm>
+#include <type_traits>
 #include "mc_device.h"
 
 namespace mc {
@@ -75,9 +76,12 @@ constexpr int kQueue = 2048;         // spike ids queued in LDS (power of two, >
 constexpr int kW0Ids = 4;            // spike ids in word 0 of a record (9-bit block-local indices)
 constexpr int kMapBits = 48;         // targets per bitmap word
 constexpr int kMapWords = (kPersistMaxB + kMapBits - 1) / kMapBits;   // 11
-constexpr int kRounds = 4;           // load rounds of a claim (64 / lanes-per-id ids each)
-constexpr int kPasses = 2;           // entries in flight per lane and round
-static_assert(1 + kMapWords <= kWinRecWords, "record words");
+// A claim of ids is delivered in rounds of 64 / lanes-per-id ids, with so many
+// entries in flight per lane and round.  A short queue (a quiet step) is shared
+// out in claims of one round, which cost the fewest instructions; a long one
+// in claims of four, which cost the fewest dependent loads.
+constexpr int kRounds = 4, kPasses = 2, kPassesShort = 4;
+static_assert(kMapWords <= kWinMapWords, "bitmap words");
 
 // Workgroups are dispatched to the XCDs round robin (workgroup g runs on XCD
 // g mod 8), and each XCD has its own L2.  The sub-rows of a source are laid
@@ -133,6 +137,17 @@ __device__ __forceinline__ int wave_incl(int x) {
   return x;
 }
 
+// A value that is the same in every lane, into a scalar register.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ unsigned uni(unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); }
+// Kernel arguments are loaded as tuples of 16 scalar registers, which spill
+// and return as a whole; what the step loop uses is copied out one by one,
+// the constants of the update into vector registers.
+template <class T>
+__device__ __forceinline__ T own_s(T x) { asm volatile("" : "+s"(x)); return x; }
+template <class T>
+__device__ __forceinline__ T own_v(T x) { asm volatile("" : "+v"(x)); return x; }
+
 // Poisson counts of the four neurons of a quad at step n, packed in bytes.
 __device__ __forceinline__ uint32_t drive_counts(long long n, uint32_t qlocal, uint64_t seed, uint32_t pops,
                                                  const uint64_t* s_table) {
@@ -179,7 +194,15 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
   const long long j0 = a.bstart[g];                                 // first owned target (padded id)
   const int Bg = a.bstart[g + 1] - a.bstart[g];                     // owned targets (multiple of 4, <= B)
   const long long n0 = *p.step_base;
-  const int DL = a.DL, B = a.B;
+  const int DL = own_s(a.DL), B = own_s(a.B), BW = own_s(a.BW), G = own_s(a.G);
+  long long* const ring = own_s(p.ring) + j0;                       // my targets' entries of slot 0
+  const unsigned ring_stride = own_s((unsigned)p.ring_stride);
+  unsigned long long* const flags = own_s(a.flags);
+  const double P11 = own_v(p.P11), P21 = own_v(p.P21), P22 = own_v(p.P22), theta = own_v(p.theta), y_reset = own_v(p.y_reset);
+  const double drift = own_v(p.P20 * p.i_e);
+  const bool drifts = p.i_e != 0.0;
+  const long long jext_q = own_v(p.jext_q);
+  const int ref_steps = own_v(p.ref_steps);
   // the queue's capacity (a test hook makes it smaller, in the phase-timing
   // instance only; a record's ids always fit)
   const unsigned qcap = (kTime && a.list_cap > 0) ? (unsigned)min(max(a.list_cap, B), kQueue) : (unsigned)kQueue;
@@ -247,15 +270,15 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (upd && pop != 0xFFu) {
       const bool free_ = (r == 0);
       if (free_) {
-        double yn = p.P22 * y + p.P21 * I;
-        if (p.i_e != 0.0) yn = yn + p.P20 * p.i_e;
+        double yn = P22 * y + P21 * I;
+        if (drifts) yn = yn + drift;
         y = yn;
       } else {
         r = r - 1;
       }
-      if (free_ && y >= p.theta) {
-        y = p.y_reset;
-        r = p.ref_steps;
+      if (free_ && y >= theta) {
+        y = y_reset;
+        r = ref_steps;
         spiked = 1;
         atomicAdd(&s_popcnt[pop], 1ull);
       }
@@ -268,17 +291,17 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     const int jl = tid;
     long long x_int = acc[slot * B + jl];
     acc[slot * B + jl] = 0;
-    unsigned* fb = &fbits[fslot * a.BW + (jl >> 5)];
+    unsigned* fb = &fbits[fslot * BW + (jl >> 5)];
     if (*fb & (1u << (jl & 31))) {
       atomicAnd(fb, ~(1u << (jl & 31)));
       x_int += (long long)__hip_atomic_exchange(
-          reinterpret_cast<unsigned long long*>(p.ring + (size_t)fslot * p.ring_stride + j0 + jl), 0ull,
+          reinterpret_cast<unsigned long long*>(ring + (size_t)fslot * ring_stride + jl), 0ull,
           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (pop != 0xFFu) x_int += (long long)kdrive * p.jext_q;
+    if (pop != 0xFFu) x_int += (long long)kdrive * jext_q;
     if (kRec && p.xrec && m - p.xrec_step0 >= 0 && m - p.xrec_step0 < p.xrec_steps)
       p.xrec[(size_t)(m - p.xrec_step0) * p.ring_stride + j0 + jl] = x_int;
-    if (pop != 0xFFu) I = p.P11 * I + (double)x_int * 0x1p-16;
+    if (pop != 0xFFu) I = P11 * I + (double)x_int * 0x1p-16;
   };
   // Compaction (thread order = id order): the ballots of the updating
   // wavefronts meet in LDS; the wavefront that arrives last sends the record
@@ -301,32 +324,37 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     const uint64_t* msk = s_mask[buf];
     const unsigned long long tag = (unsigned long long)t16m << 48;
-    unsigned long long* rec = a.flags + ((size_t)(m & (kRecSlots - 1)) * a.G + g) * kWinRecWords;
+    uint64_t mr[kPersistMaxBlock / 64];         // all masks, loaded together
+#pragma unroll
+    for (int w = 0; w < kPersistMaxBlock / 64; ++w) mr[w] = msk[w];   // (zero beyond nupd)
+    const int mapw = (kMapBits * lane) >> 6, sh = (kMapBits * lane) & 63;   // lane L < 11 holds targets 48L..48L+47
+    const uint64_t m_lo = msk[min(mapw, kPersistMaxBlock / 64)], m_hi = msk[min(mapw + 1, kPersistMaxBlock / 64)];
     int nloc = 0;
-    for (int w = 0; w < nupd; ++w) nloc += __popcll(msk[w]);
-    nloc = __builtin_amdgcn_readfirstlane(nloc);
+#pragma unroll
+    for (int w = 0; w < kPersistMaxBlock / 64; ++w) nloc += __popcll(mr[w]);
+    nloc = uni(nloc);
     unsigned long long f = 0;
     if (nloc > kW0Ids) {
-      // lane L holds targets 48L..48L+47
-      const int b = kMapBits * lane, w = min(b >> 6, nupd), sh = b & 63;
-      unsigned long long v = msk[w] >> sh;
-      if (sh > 64 - kMapBits) v |= msk[min(w + 1, nupd)] << (64 - sh);
+      unsigned long long v = m_lo >> sh;
+      if (sh > 64 - kMapBits) v |= m_hi << (64 - sh);
       v &= (1ull << kMapBits) - 1;
       if (lane >= kMapWords) v = 0;
       f = __ballot(v != 0);
-      if (v != 0) st_dev(&rec[1 + lane], tag | v);
-    } else {
+      if (v != 0) st_dev(&flags[window_map(G, (int)(m & (kRecSlots - 1)), g) + lane], tag | v);
+    } else if (nloc > 0) {
       int k = 0;
-      for (int w = 0; w < nupd && k < nloc; ++w)
-        for (uint64_t mm = msk[w]; mm; mm &= mm - 1, ++k) f |= (unsigned long long)(64 * w + __builtin_ctzll(mm)) << (9 * k);
+#pragma unroll
+      for (int w = 0; w < kPersistMaxBlock / 64; ++w)
+        for (uint64_t mm = mr[w]; mm; mm &= mm - 1, ++k) f |= (unsigned long long)(64 * w + __builtin_ctzll(mm)) << (9 * k);
     }
-    if (lane == 0) st_dev(&rec[0], tag | (unsigned long long)nloc << 36 | f);
+    if (lane == 0) st_dev(&flags[window_word0(G, (int)(m & (kRecSlots - 1)), g)], tag | (unsigned long long)nloc << 36 | f);
     if (nloc == 0) return;
     const long long rcnt = s_rcnt;
     if (rcnt + nloc <= p.raster_cap) {
       int2* out = p.raster + (size_t)g * p.raster_cap + rcnt;
-      for (int w = 0; w < nupd; ++w) {
-        const uint64_t mm = msk[w];
+#pragma unroll
+      for (int w = 0; w < kPersistMaxBlock / 64; ++w) {
+        const uint64_t mm = mr[w];
         if ((mm >> lane) & 1ull)
           out[__popcll(mm & (lane ? (~0ull >> (64 - lane)) : 0ull))] = make_int2((int)m, (int)(j0 + 64 * w + lane));
         out += __popcll(mm);
@@ -364,7 +392,7 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
 #pragma unroll
         for (int u = 0; u < kPro; ++u) {
           const int m = m0 + u * nw;
-          v[u] = (m < scan) ? ld_dev(p.ring + (size_t)((rs0 + m) & kRingMask) * p.ring_stride + j0 + jl) : 0ll;
+          v[u] = (m < scan) ? ld_dev(ring + (size_t)((rs0 + m) & kRingMask) * ring_stride + jl) : 0ll;
         }
 #pragma unroll
         for (int u = 0; u < kPro; ++u) {
@@ -373,9 +401,9 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
           if (m < take) {
             const int s = sl0 + m;
             acc[(s >= DL ? s - DL : s) * B + jl] = v[u];
-            st_dev(p.ring + (size_t)rs * p.ring_stride + j0 + jl, 0ll);
+            st_dev(ring + (size_t)rs * ring_stride + jl, 0ll);
           } else if (m >= DL) {
-            atomicOr(&fbits[rs * a.BW + (jl >> 5)], 1u << (jl & 31));
+            atomicOr(&fbits[rs * BW + (jl >> 5)], 1u << (jl & 31));
           }
         }
       }
@@ -387,6 +415,10 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
   // ---- step loop of a wavefront ------------------------------------------------
   const int ls = a.lsh;                       // lanes per id of a delivery: 1 << ls
   const int sub = lane >> ls, sl_lane = lane & ((1 << ls) - 1), per = 64 >> ls;
+  const unsigned* const off = own_s(a.off) + gpos;   // sub-row bounds of this workgroup in row 0
+  const unsigned long long* const pk = own_s(a.pk);
+  const int64_t* const row_ptr = own_s(p.row_ptr);
+  const long long wait_ticks = own_s(a.wait_ticks);
   unsigned long long ev = 0;                  // synaptic events delivered by this lane's sub-rows
   int uit = 0, un = (int)(n0 % DL);           // next update (step n0 + uit) and its LDS slot
   int pit = 0, pn = (int)(n0 % DL);           // the poller's step and its LDS slot
@@ -402,6 +434,85 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     }
     todo = todo_all;
   }
+  // Adds every event of ids [h, h + c) of the queue, in R rounds with P entries
+  // in flight per lane and round (c <= R * per).
+  const unsigned B8 = (unsigned)B * 8u, win = own_s((unsigned)DL * B8);   // bytes of a slot and of the window
+  const unsigned near_span = (unsigned)(DL - 2) * B8;    // offsets B8 .. B8 + near_span - 1: delays 1 .. DL-2
+  unsigned char* const acc_b = reinterpret_cast<unsigned char*>(acc);
+  auto deliver = [&](auto rc, auto pc, unsigned h, unsigned c) {
+    constexpr int R = decltype(rc)::value, P = decltype(pc)::value;
+    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];     // (lanes >= c unused)
+    const unsigned long long* ent[R];
+    int len[R];
+    unsigned sn[R];                                         // byte offset of the spike's slot
+    int longest = 0;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int idx = k * per + sub;
+      const unsigned q = (unsigned)__shfl((int)qq, idx, 64);
+      const bool mine = idx < (int)c;
+      const unsigned id = mine ? q & 0x3FFFFu : 0u;
+      const unsigned* o = off + (size_t)id * (unsigned)(G + 1);
+      const unsigned o0 = o[0], o1 = o[1];
+      ent[k] = pk + (row_ptr[id] + o0 + sl_lane);
+      len[k] = mine ? (int)(o1 - o0) : 0;
+      sn[k] = __umul24((q >> 18) & 0x7Fu, B8);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (sl_lane == 0) ev += (unsigned)len[k];
+      len[k] -= sl_lane;                                    // entries of this lane: 0, L, 2L, ... < len
+      longest = max(longest, len[k]);
+    }
+    bool far = false;
+    for (int e = 0; __any(e < longest); e += P << ls) {
+      unsigned long long v[R][P];
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+          v[k][u] = 0;
+          if (e + (u << ls) < len[k]) v[k][u] = ent[k][e + (u << ls)];
+        }
+      bool beyond = false;                                  // some event of this pass lies beyond the window
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+          const unsigned hi = (unsigned)(v[k][u] >> 32);    // (delay * B + local target) * 8; 0: no entry
+          const unsigned at = sn[k] + hi;
+          beyond |= hi >= B8 + near_span;
+          if (hi - B8 < near_span)
+            atomicAdd(reinterpret_cast<unsigned long long*>(acc_b + min(at, at - win)),   // modulo the window
+                      (unsigned long long)(long long)(int)(v[k][u] & 0xFFFFFFFFu));
+        }
+      if (__any(beyond)) {                                  // rare
+        far = true;
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+          for (int u = 0; u < P; ++u) {
+            const unsigned hi = (unsigned)(v[k][u] >> 32);
+            const unsigned q = (unsigned)__shfl((int)qq, k * per + sub, 64);
+            if (hi < B8 + near_span) continue;
+            const int d = (int)(hi / B8), jl = (int)((hi - (unsigned)d * B8) >> 3);
+            const int fs = ((int)(q >> 25) + d) & kRingMask;
+            atomicAdd(reinterpret_cast<unsigned long long*>(ring + (size_t)fs * ring_stride + jl),
+                      (unsigned long long)(long long)(int)(v[k][u] & 0xFFFFFFFFu));
+            atomicOr(&fbits[fs * BW + (jl >> 5)], 1u << (jl & 31));
+          }
+      }
+    }
+    // far adds are complete before the ids count as delivered
+    if (far) __builtin_amdgcn_s_waitcnt(0);
+    for (unsigned long long rem = c >= 64 ? ~0ull : (1ull << c) - 1; rem;) {   // a claim may span steps
+      const unsigned st = (unsigned)__builtin_amdgcn_readlane((int)qq, __builtin_ctzll(rem)) >> 25 & 3u;
+      const unsigned long long same = __ballot((qq >> 25 & 3u) == st) & rem;
+      rem &= ~same;
+      if (lane == 0)
+        __hip_atomic_fetch_add(&s_done[st], (unsigned)__popcll(same), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  };
   unsigned spins = 0;
   long long t_wait = 0;                       // wall clock at the first check of a wait (0: not waiting)
   long long tp_idle = kTime ? wall_clock64() : 0;
@@ -412,9 +523,9 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (isU && uit < steps) {
       const long long n = n0 + uit;
       bool ready = uit == 0;
-      if (!ready && lds_acq(&s_listed) >= uit) {
+      if (!ready && uni(lds_acq(&s_listed)) >= uit) {
         const int k = (int)((n - 1) & 3);
-        ready = lds_acq(&s_done[k]) == s_end[k];
+        ready = uni(lds_acq(&s_done[k]) - s_end[k]) == 0;
       }
       if (ready) {
         long long tp = 0;
@@ -444,44 +555,54 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (isP && pit < steps && (!isU || pit <= uit)) {
       const long long tq = kTime ? wall_clock64() : 0;
       const long long n = n0 + pit;
-      const unsigned long long* recs = a.flags + (size_t)(n & (kRecSlots - 1)) * a.G * kWinRecWords;
-      const unsigned long long tag = (unsigned long long)t16p << 48;
+      const int rslot = (int)(n & (kRecSlots - 1));
+      const unsigned long long* recs = flags + window_word0(G, rslot, 0);
       const unsigned qtag = (unsigned)pn << 18 | (unsigned)(n & kRingMask) << 25;
       const unsigned tail0 = tail;
       const volatile unsigned* done = s_done;   // ids delivered by now (the queue's room)
       unsigned long long w0[kPoll];
 #pragma unroll
-      for (int k = 0; k < kPoll; ++k)
-        w0[k] = ((todo >> k) & 1u) ? ld_dev(&recs[(size_t)(lane + 64 * k) * kWinRecWords]) : 0ull;
+      for (int k = 0; k < kPoll; ++k) w0[k] = ((todo >> k) & 1u) ? ld_dev(&recs[(lane + 64 * k) * kWord0Stride]) : 0ull;
       const unsigned gone = done[0] + done[1] + done[2] + done[3];
+      unsigned busy = 0;                        // the k in which some record holds spikes
 #pragma unroll
       for (int k = 0; k < kPoll; ++k) {
         const bool seen = ((todo >> k) & 1u) && (w0[k] >> 48) == t16p;
-        const int c = seen ? (int)((w0[k] >> 36) & 0xFFFu) : 0;
-        if (!__any(c > 0)) {                    // nothing but empty records
-          if (seen) todo &= ~(1u << k);
-          continue;
+        const bool some = seen && ((w0[k] >> 36) & 0xFFFu) != 0;
+        if (seen && !some) todo &= ~(1u << k);  // an empty record
+        if (__any(some)) busy |= 1u << k;
+      }
+#pragma unroll 1
+      for (; busy; busy &= busy - 1) {
+        const int k = __builtin_ctz(busy);
+        unsigned long long w = w0[0];
+        long long first = pbs[0];
+#pragma unroll
+        for (int u = 1; u < kPoll; ++u) {
+          w = (u == k) ? w0[u] : w;
+          first = (u == k) ? pbs[u] : first;
         }
-        bool ok = seen;
-        unsigned long long wk[kMapWords];
+        const int c = (((todo >> k) & 1u) && (w >> 48) == t16p) ? (int)((w >> 36) & 0xFFFu) : 0;
+        bool ok = c > 0;
         const bool maps = c > kW0Ids;
+        unsigned long long wk[kMapWords];
         const bool any_maps = __any(maps);
         if (any_maps) {
+          const unsigned long long* mw = flags + window_map(G, rslot, lane + 64 * k);
+          const unsigned long long tag = (unsigned long long)t16p << 48;
 #pragma unroll
-          for (int L = 0; L < kMapWords; ++L)
-            wk[L] = (maps && ((w0[k] >> L) & 1ull)) ? ld_dev(&recs[(size_t)(lane + 64 * k) * kWinRecWords + 1 + L]) : tag;
+          for (int L = 0; L < kMapWords; ++L) wk[L] = (maps && ((w >> L) & 1ull)) ? ld_dev(&mw[L]) : tag;
 #pragma unroll
           for (int L = 0; L < kMapWords; ++L) ok &= (wk[L] >> 48) == t16p;
         }
-        const int cc = ok ? c : 0;
-        const int x = wave_incl(cc);
+        const int x = wave_incl(ok ? c : 0);
         ok = ok && x <= (int)(qcap - (tail - gone));   // room in the queue
-        if (ok) todo &= ~(1u << k);
-        if (ok && c > 0) {
+        if (ok) {
+          todo &= ~(1u << k);
           unsigned o = tail + (unsigned)(x - c);
-          const unsigned b = (unsigned)pbs[k] | qtag;   // ids < 2^18, and pbs + local index too: no carry
+          const unsigned b = (unsigned)first | qtag;   // ids < 2^18, and first + local index too: no carry
           if (!maps) {
-            for (int e = 0; e < c; ++e) s_q[o++ & (kQueue - 1)] = b + (unsigned)((w0[k] >> (9 * e)) & 0x1FFull);
+            for (int e = 0; e < c; ++e) s_q[o++ & (kQueue - 1)] = b + (unsigned)((w >> (9 * e)) & 0x1FFull);
           } else {
 #pragma unroll
             for (int L = 0; L < kMapWords; ++L)
@@ -489,8 +610,8 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
                 s_q[o++ & (kQueue - 1)] = b + (unsigned)(kMapBits * L + __builtin_ctzll(mm));
           }
         }
-        // the accepted lanes are a prefix of those with ids
-        const unsigned long long acc_m = __ballot(ok && c > 0);
+        // the accepted lanes are a prefix of those with complete records
+        const unsigned long long acc_m = __ballot(ok);
         if (acc_m) tail += (unsigned)__builtin_amdgcn_readlane(x, 63 - __builtin_clzll(acc_m));
       }
       progress = tail != tail0;
@@ -515,12 +636,12 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (delivers || (pit == steps && uit >= (isU ? steps : 0))) {
       unsigned h = 0, c = 0;
       {
-        const unsigned t = lds_acq(&s_tail);
-        h = *(volatile unsigned*)&s_head;         // (may be past t by now)
+        const unsigned t = uni(lds_acq(&s_tail));
+        h = uni(*(volatile unsigned*)&s_head);    // (may be past t by now)
         if ((int)(t - h) > 0) {
           if (lane == 0) {
             while ((int)(t - h) > 0) {
-              const unsigned want = min(t - h, (unsigned)(kRounds * per));
+              const unsigned want = min(t - h, (unsigned)(t - h > (unsigned)(nw * per) ? kRounds * per : per));
               if (__hip_atomic_compare_exchange_strong(&s_head, &h, h + want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_WORKGROUP)) {
                 c = want;
@@ -528,72 +649,14 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
               }
             }
           }
-          h = (unsigned)__builtin_amdgcn_readfirstlane((int)h);
-          c = (unsigned)__builtin_amdgcn_readfirstlane((int)c);
+          h = uni(h);
+          c = uni(c);
         }
       }
       if (c > 0) {
         const long long tq = kTime ? wall_clock64() : 0;
-        const unsigned qq = s_q[(h + lane) & (kQueue - 1)];     // (lanes >= c unused)
-        const unsigned long long* ent[kRounds];
-        int len[kRounds];
-        unsigned sn[kRounds];
-        int longest = 0;
-#pragma unroll
-        for (int k = 0; k < kRounds; ++k) {
-          len[k] = 0;
-          const int idx = k * per + sub;
-          sn[k] = (unsigned)__shfl((int)qq, idx, 64);
-          if (idx < (int)c) {
-            const unsigned id = sn[k] & 0x3FFFFu;
-            const unsigned* o = a.off + (size_t)id * (unsigned)(a.G + 1) + (unsigned)gpos;
-            const unsigned o0 = o[0], o1 = o[1];
-            ent[k] = a.pk + (p.row_ptr[id] + o0 + sl_lane);
-            len[k] = (int)(o1 - o0);
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < kRounds; ++k) {
-          if (sl_lane == 0) ev += (unsigned long long)len[k];
-          len[k] -= sl_lane;                                    // entries of this lane: 0, L, 2L, ... < len
-          longest = max(longest, len[k]);
-        }
-        bool far_any = false;
-        for (int e = 0; __any(e < longest); e += kPasses << ls) {
-          unsigned long long v[kRounds][kPasses];
-#pragma unroll
-          for (int k = 0; k < kRounds; ++k)
-#pragma unroll
-            for (int u = 0; u < kPasses; ++u) v[k][u] = (e + (u << ls) < len[k]) ? ent[k][e + (u << ls)] : 0ull;
-#pragma unroll
-          for (int k = 0; k < kRounds; ++k)
-#pragma unroll
-            for (int u = 0; u < kPasses; ++u) {
-              if (v[k][u] == 0) continue;
-              const unsigned hi = (unsigned)(v[k][u] >> 32);
-              const int d = (int)(hi >> 16), jl = (int)(hi & 0xFFFFu);
-              const unsigned long long w = (unsigned long long)(long long)(int)(v[k][u] & 0xFFFFFFFFu);
-              if (d <= DL - 2) {
-                int s = (int)((sn[k] >> 18) & 0x7Fu) + d;
-                if (s >= DL) s -= DL;
-                atomicAdd(reinterpret_cast<unsigned long long*>(&acc[s * B + jl]), w);
-              } else {
-                const int fs = (int)(((sn[k] >> 25) + (unsigned)d) & (unsigned)kRingMask);
-                atomicAdd(reinterpret_cast<unsigned long long*>(p.ring + (size_t)fs * p.ring_stride + j0 + jl), w);
-                atomicOr(&fbits[fs * a.BW + (jl >> 5)], 1u << (jl & 31));
-                far_any = true;
-              }
-            }
-        }
-        // far adds are complete before the ids count as delivered
-        if (__any(far_any)) __builtin_amdgcn_s_waitcnt(0);
-        for (unsigned long long rem = c >= 64 ? ~0ull : (1ull << c) - 1; rem;) {   // a claim may span steps
-          const unsigned st = (unsigned)__builtin_amdgcn_readlane((int)qq, __builtin_ctzll(rem)) >> 25 & 3u;
-          const unsigned long long same = __ballot((qq >> 25 & 3u) == st) & rem;
-          rem &= ~same;
-          if (lane == 0)
-            __hip_atomic_fetch_add(&s_done[st], (unsigned)__popcll(same), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
+        if (c <= (unsigned)per) deliver(std::integral_constant<int, 1>(), std::integral_constant<int, kPassesShort>(), h, c);
+        else deliver(std::integral_constant<int, kRounds>(), std::integral_constant<int, kPasses>(), h, c);
         if (kTime) { const long long t = wall_clock64(); ph[4] += t - tq; tp_idle += t - tq; }
         t_wait = 0;
         continue;
@@ -601,16 +664,16 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     }
     if (progress) { t_wait = 0; continue; }
     // ---- nothing to do now -------------------------------------------------------
-    if ((!isU || uit == steps) && (!isP || pit == steps) && *(volatile int*)&s_listed == steps &&
-        *(volatile unsigned*)&s_head == lds_acq(&s_tail))
+    if ((!isU || uit == steps) && (!isP || pit == steps) && uni(lds_acq(&s_listed)) == steps &&
+        uni(*(volatile unsigned*)&s_head - *(volatile unsigned*)&s_tail) == 0)
       break;
-    if (*(volatile int*)&s_abort) break;
+    if (uni(*(volatile int*)&s_abort)) break;
     if (!isU) __builtin_amdgcn_s_sleep(1);
     // (a wavefront that only delivers may rightly idle for long)
     if ((isP || isU) && (++spins & 255u) == 0u) {   // the wall clock is read every 256 rounds only
       const long long t = wall_clock64();
       if (t_wait == 0) t_wait = t;
-      else if (t - t_wait > a.wait_ticks) {
+      else if (t - t_wait > wait_ticks) {
         if (lane == 0) atomicOr(p.overflow, 2u);
         s_abort = 1;
         break;
@@ -643,8 +706,8 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
       for (int jl = lane; jl < Bg; jl += 64) {
         const long long v = acc[s * B + jl];
         if (v == 0) continue;
-        long long* e = p.ring + (size_t)rs * p.ring_stride + j0 + jl;
-        if (fbits[rs * a.BW + (jl >> 5)] & (1u << (jl & 31)))
+        long long* e = ring + (size_t)rs * ring_stride + jl;
+        if (fbits[rs * BW + (jl >> 5)] & (1u << (jl & 31)))
           atomicAdd(reinterpret_cast<unsigned long long*>(e), (unsigned long long)v);
         else
           st_dev(e, v);
@@ -691,7 +754,7 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_exchange_probe(unsigned lo
   for (long long n = 0; n < steps; ++n) {
     const unsigned long long tag16 = (unsigned long long)((n + 1) % 65535 + 1) << 48;
     const size_t rslot = (size_t)(n % kRecSlots);
-    if (tid == 0) st_dev(&flags[(rslot * G + g) * kWinRecWords], tag16);
+    if (tid == 0) st_dev(&flags[window_word0(G, (int)rslot, g)], tag16);
     if (wave == nw - 1) {
       long long t_poll = 0;          // the wall clock is read every 256 rounds only
       unsigned spins = 0;
@@ -703,7 +766,7 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_exchange_probe(unsigned lo
         unsigned long long w0[kPoll];
 #pragma unroll
         for (int r = 0; r < kPoll; ++r)
-          w0[r] = ((todo >> r) & 1u) ? ld_dev(&flags[(rslot * G + lane + 64 * r) * kWinRecWords])
+          w0[r] = ((todo >> r) & 1u) ? ld_dev(&flags[window_word0(G, (int)rslot, lane + 64 * r)])
                                      : 0ull;
 #pragma unroll
         for (int r = 0; r < kPoll; ++r)
@@ -747,8 +810,9 @@ hipError_t launch_exchange_probe(unsigned long long* flags, int G, int block, lo
 }
 
 // Packed rows: row i's synapses reordered by target workgroup, the workgroups
-// in XCD order, as delay << 48 | local target << 32 | weight (in the row's
-// order inside a sub-row); off[i][q] = first entry of the workgroup at place q,
+// in XCD order, as (delay * B + local target) * 8 << 32 | weight (the byte
+// offset into the LDS window from the spike's slot; in the row's order inside
+// a sub-row); off[i][q] = first entry of the workgroup at place q,
 // off[i][G] = the row's length.  One workgroup per row: a histogram over the
 // target workgroups, its two prefix sums (target order and XCD order), then
 // every entry to its place.
@@ -802,7 +866,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_rows(const int64_t* row_ptr
   __syncthreads();
   for (int k = tid; k < len; k += kPackBlock) {
     const int t = tgt[b + k], g = t / B;
-    pk[b + k + s_cnt[g]] = (unsigned long long)dly[b + k] << 48 | (unsigned long long)(unsigned)(t - g * B) << 32 |
+    pk[b + k + s_cnt[g]] = (unsigned long long)(8u * ((unsigned)dly[b + k] * (unsigned)B + (unsigned)(t - g * B))) << 32 |
                            (unsigned)wq[b + k];
   }
 }
