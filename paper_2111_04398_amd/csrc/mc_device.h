@@ -112,7 +112,8 @@ __host__ __device__ inline size_t window_map(int G, int slot, int g) {
 __host__ __device__ inline size_t window_record_words(int G) { return window_map(G, kRecSlots, 0); }
 __host__ __device__ inline size_t window_flag_words(int G) { return window_record_words(G) + kPersistFlagStride; }
 constexpr int kPersistMaxB = 512;       // owned targets per workgroup (one per thread)
-constexpr int kPersistMaxBlock = 512;   // threads per workgroup: 256 VGPRs per lane, no scratch spills
+constexpr int kPersistMaxBlock = 512;   // threads per workgroup of a launch configuration
+constexpr int kPersistThreads = 768;   // threads of a workgroup alone on its compute unit: 168 VGPRs per lane
 size_t persist_lds_bytes(int G, int B, int DL);
 // Fills the packed rows and their sub-row bounds for G workgroups of B targets.
 hipError_t launch_pack_rows(const int64_t* row_ptr, const int32_t* tgt, const int32_t* wq, const uint8_t* dly,
@@ -120,7 +121,7 @@ hipError_t launch_pack_rows(const int64_t* row_ptr, const int32_t* tgt, const in
 hipError_t persist_static_lds(size_t* bytes);
 hipError_t persist_occupancy(int block, size_t lds, int* blocks_per_cu);
 hipError_t persist_set_lds_limit(size_t lds);
-hipError_t launch_persist(const DevNet& p, const PersistArgs& a, int steps, int block, hipStream_t s);
+hipError_t launch_persist(const DevNet& p, const PersistArgs& a, int steps, int threads, hipStream_t s);
 // Scratch of the allocation-free entry point (mc_noalloc.hip): the spike
 // records of this device (room for 512 workgroups); and a record clear by kernel.
 size_t noalloc_record_words();

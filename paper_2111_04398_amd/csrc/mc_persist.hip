@@ -65,7 +65,6 @@
 #pragma clang fp contract(off)
 
 #include <algorithm>
-#include <type_traits>
 #include "mc_device.h"
 
 namespace mc {
@@ -76,11 +75,10 @@ constexpr int kQueue = 2048;         // spike ids queued in LDS (power of two, >
 constexpr int kW0Ids = 4;            // spike ids in word 0 of a record (9-bit block-local indices)
 constexpr int kMapBits = 48;         // targets per bitmap word
 constexpr int kMapWords = (kPersistMaxB + kMapBits - 1) / kMapBits;   // 11
-// A claim of ids is delivered in rounds of 64 / lanes-per-id ids, with so many
-// entries in flight per lane and round.  A short queue (a quiet step) is shared
-// out in claims of one round, which cost the fewest instructions; a long one
-// in claims of four, which cost the fewest dependent loads.
-constexpr int kRounds = 4, kPasses = 2, kPassesShort = 4;
+// Deliveries (see deliver_few and deliver_many): entries in flight per lane of
+// a short claim; units listed per wavefront, and slots of a group in flight, of
+// a long one.
+constexpr int kFew = 4, kUnits = 64, kSlots = 4;
 static_assert(kMapWords <= kWinMapWords, "bitmap words");
 
 // Workgroups are dispatched to the XCDs round robin (workgroup g runs on XCD
@@ -121,6 +119,10 @@ __device__ __forceinline__ T lds_acq(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 template <class T>
+__device__ __forceinline__ T lds_rlx(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <class T>
 __device__ __forceinline__ void lds_rel(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -145,6 +147,15 @@ __device__ __forceinline__ unsigned uni(unsigned x) { return (unsigned)__builtin
 // the constants of the update into vector registers.
 template <class T>
 __device__ __forceinline__ T own_s(T x) { asm volatile("" : "+s"(x)); return x; }
+// (a pointer comes back as one to global memory: as a generic pointer its
+// accesses would be flat ones, which count as LDS accesses too)
+template <class T>
+__device__ __forceinline__ T* own_p(T* x) {
+  typedef __attribute__((address_space(1))) T* global_ptr;
+  unsigned long long v = (unsigned long long)x;
+  asm volatile("" : "+s"(v));
+  return (T*)(global_ptr)v;
+}
 template <class T>
 __device__ __forceinline__ T own_v(T x) { asm volatile("" : "+v"(x)); return x; }
 
@@ -153,8 +164,8 @@ __device__ __forceinline__ uint32_t drive_counts(long long n, uint32_t qlocal, u
                                                  const uint64_t* s_table) {
   const U64x4 v = philox4x64_10((uint64_t)n, (uint64_t)qlocal, 0, kTagDrive, seed, 0);
   uint32_t out = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
+#pragma unroll 1
+  for (int k = 0; k < 4; ++k) {               // (not unrolled: the step loop's code has to stay in the instruction cache)
     const unsigned pop = (pops >> (8 * k)) & 0xFFu;
     if (pop == 0xFFu) continue;
     out |= (uint32_t)poisson_inv(s_table + pop * kTableLen, hi32(pick(v, k))) << (8 * k);
@@ -164,13 +175,14 @@ __device__ __forceinline__ uint32_t drive_counts(long long n, uint32_t qlocal, u
 
 }  // namespace
 
-// LDS (dynamic): acc[DL*B] i64 | fbits[128*BW] u32 | s_q[kQueue] u32
+// LDS (dynamic): acc[DL*B] i64 | fbits[128*BW] u32 | s_q[kQueue] u32 |
+//                s_units[16][kUnits] 16 bytes (B is a multiple of 4: all aligned)
 // kRec: the adjoint's forward recording (input x and state checkpoints);
 // kTime: phase timestamps.  Plain simulation runs the instance with neither
 // (fewer registers).  kPoll: producers polled per lane (4 when G <= 256: a
 // smaller poll loop, fewer registers; else 8).
 template <bool kRec, bool kTime, int kPoll>
-__global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistArgs a, int steps) {
+__global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistArgs a, int steps) {
   extern __shared__ __align__(16) unsigned char s_raw[];
   __shared__ __align__(16) uint64_t s_table[kMaxPops * kTableLen];
   __shared__ uint64_t s_mask[4][kPersistMaxBlock / 64 + 1];   // spike ballots per wavefront, by epoch mod 4 (last: 0)
@@ -180,12 +192,14 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
   __shared__ int s_abort, s_last;
   // The id queue: ids [0, s_tail) have been put in, [0, s_head) claimed; of
   // the steps = k (mod 4), s_end[k] ids in listed steps, s_done[k] delivered.
-  __shared__ unsigned s_tail, s_head, s_end[4], s_done[4];
+  // s_endq: s_tail after the last step = k (mod 4).
+  __shared__ unsigned s_tail, s_head, s_end[4], s_done[4], s_endq[4];
   __shared__ int s_listed;                       // steps of this launch whose records are all in the queue
   __shared__ unsigned s_arr[2];                  // arrivals of the updating wavefronts, by epoch parity (monotonic)
   long long* acc = reinterpret_cast<long long*>(s_raw);
   unsigned* fbits = reinterpret_cast<unsigned*>(acc + (size_t)a.DL * a.B);
   unsigned* s_q = fbits + 128 * a.BW;
+  uint4* s_units = reinterpret_cast<uint4*>(s_q + kQueue);          // [wavefronts][kUnits] 
 
   const int g = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int lane = tid & 63, nw = nthr >> 6;
@@ -195,9 +209,9 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
   const int Bg = a.bstart[g + 1] - a.bstart[g];                     // owned targets (multiple of 4, <= B)
   const long long n0 = *p.step_base;
   const int DL = own_s(a.DL), B = own_s(a.B), BW = own_s(a.BW), G = own_s(a.G);
-  long long* const ring = own_s(p.ring) + j0;                       // my targets' entries of slot 0
+  long long* const ring = own_p(p.ring) + j0;                       // my targets' entries of slot 0
   const unsigned ring_stride = own_s((unsigned)p.ring_stride);
-  unsigned long long* const flags = own_s(a.flags);
+  unsigned long long* const flags = own_p(a.flags);
   const double P11 = own_v(p.P11), P21 = own_v(p.P21), P22 = own_v(p.P22), theta = own_v(p.theta), y_reset = own_v(p.y_reset);
   const double drift = own_v(p.P20 * p.i_e);
   const bool drifts = p.i_e != 0.0;
@@ -415,97 +429,47 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
   // ---- step loop of a wavefront ------------------------------------------------
   const int ls = a.lsh;                       // lanes per id of a delivery: 1 << ls
   const int sub = lane >> ls, sl_lane = lane & ((1 << ls) - 1), per = 64 >> ls;
-  const unsigned* const off = own_s(a.off) + gpos;   // sub-row bounds of this workgroup in row 0
-  const unsigned long long* const pk = own_s(a.pk);
-  const int64_t* const row_ptr = own_s(p.row_ptr);
+  const unsigned* const off = own_p(a.off) + gpos;   // sub-row bounds of this workgroup in row 0
+  const unsigned long long* const pk = own_p(a.pk);
+  const int64_t* const row_ptr = own_p(p.row_ptr);
   const long long wait_ticks = own_s(a.wait_ticks);
   unsigned long long ev = 0;                  // synaptic events delivered by this lane's sub-rows
   int uit = 0, un = (int)(n0 % DL);           // next update (step n0 + uit) and its LDS slot
   int pit = 0, pn = (int)(n0 % DL);           // the poller's step and its LDS slot
   unsigned t16p = t16_0, tail = 0;            // its tag; ids put into the queue
-  long long pbs[kPoll];                       // first owned target of each producer this lane polls
   unsigned todo = 0, todo_all = 0;            // producers of the step still to be seen
   if (isP) {
 #pragma unroll
-    for (int k = 0; k < kPoll; ++k) {
-      const int h = lane + 64 * k;
-      pbs[k] = (h < a.G) ? a.bstart[h] : 0;
-      if (h < a.G) todo_all |= 1u << k;
-    }
+    for (int k = 0; k < kPoll; ++k)
+      if (lane + 64 * k < G) todo_all |= 1u << k;
     todo = todo_all;
   }
-  // Adds every event of ids [h, h + c) of the queue, in R rounds with P entries
-  // in flight per lane and round (c <= R * per).
   const unsigned B8 = (unsigned)B * 8u, win = own_s((unsigned)DL * B8);   // bytes of a slot and of the window
   const unsigned near_span = (unsigned)(DL - 2) * B8;    // offsets B8 .. B8 + near_span - 1: delays 1 .. DL-2
   unsigned char* const acc_b = reinterpret_cast<unsigned char*>(acc);
-  auto deliver = [&](auto rc, auto pc, unsigned h, unsigned c) {
-    constexpr int R = decltype(rc)::value, P = decltype(pc)::value;
-    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];     // (lanes >= c unused)
-    const unsigned long long* ent[R];
-    int len[R];
-    unsigned sn[R];                                         // byte offset of the spike's slot
-    int longest = 0;
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const int idx = k * per + sub;
-      const unsigned q = (unsigned)__shfl((int)qq, idx, 64);
-      const bool mine = idx < (int)c;
-      const unsigned id = mine ? q & 0x3FFFFu : 0u;
-      const unsigned* o = off + (size_t)id * (unsigned)(G + 1);
-      const unsigned o0 = o[0], o1 = o[1];
-      ent[k] = pk + (row_ptr[id] + o0 + sl_lane);
-      len[k] = mine ? (int)(o1 - o0) : 0;
-      sn[k] = __umul24((q >> 18) & 0x7Fu, B8);
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-      if (sl_lane == 0) ev += (unsigned)len[k];
-      len[k] -= sl_lane;                                    // entries of this lane: 0, L, 2L, ... < len
-      longest = max(longest, len[k]);
-    }
-    bool far = false;
-    for (int e = 0; __any(e < longest); e += P << ls) {
-      unsigned long long v[R][P];
-#pragma unroll
-      for (int k = 0; k < R; ++k)
-#pragma unroll
-        for (int u = 0; u < P; ++u) {
-          v[k][u] = 0;
-          if (e + (u << ls) < len[k]) v[k][u] = ent[k][e + (u << ls)];
-        }
-      bool beyond = false;                                  // some event of this pass lies beyond the window
-#pragma unroll
-      for (int k = 0; k < R; ++k)
-#pragma unroll
-        for (int u = 0; u < P; ++u) {
-          const unsigned hi = (unsigned)(v[k][u] >> 32);    // (delay * B + local target) * 8; 0: no entry
-          const unsigned at = sn[k] + hi;
-          beyond |= hi >= B8 + near_span;
-          if (hi - B8 < near_span)
-            atomicAdd(reinterpret_cast<unsigned long long*>(acc_b + min(at, at - win)),   // modulo the window
-                      (unsigned long long)(long long)(int)(v[k][u] & 0xFFFFFFFFu));
-        }
-      if (__any(beyond)) {                                  // rare
-        far = true;
-#pragma unroll
-        for (int k = 0; k < R; ++k)
-#pragma unroll
-          for (int u = 0; u < P; ++u) {
-            const unsigned hi = (unsigned)(v[k][u] >> 32);
-            const unsigned q = (unsigned)__shfl((int)qq, k * per + sub, 64);
-            if (hi < B8 + near_span) continue;
-            const int d = (int)(hi / B8), jl = (int)((hi - (unsigned)d * B8) >> 3);
-            const int fs = ((int)(q >> 25) + d) & kRingMask;
-            atomicAdd(reinterpret_cast<unsigned long long*>(ring + (size_t)fs * ring_stride + jl),
-                      (unsigned long long)(long long)(int)(v[k][u] & 0xFFFFFFFFu));
-            atomicOr(&fbits[fs * BW + (jl >> 5)], 1u << (jl & 31));
-          }
-      }
-    }
-    // far adds are complete before the ids count as delivered
+  // One event: packed entry e of a spike whose slot starts at byte sn of the
+  // window (entry 0 or sn kNone: the lane has none here).
+  // Returns whether it lies beyond the window (add_far).
+  constexpr unsigned kNone = 0x80000000u;
+  auto add = [&](unsigned long long e, unsigned sn) __attribute__((always_inline)) -> bool {
+    const unsigned hi = (int)sn < 0 ? 0u : (unsigned)(e >> 32), at = sn + hi;
+    if (hi - B8 < near_span)
+      atomicAdd(reinterpret_cast<unsigned long long*>(acc_b + min(at, at - win)),   // modulo the window
+                (unsigned long long)(long long)(int)(e & 0xFFFFFFFFu));
+    return hi >= B8 + near_span;
+  };
+  auto add_far = [&](unsigned long long e, unsigned rs) {   // rs: the spike's ring slot
+    const unsigned hi = (unsigned)(e >> 32);
+    const unsigned d = hi / B8, jl = (hi - d * B8) >> 3, fs = (rs + d) & (unsigned)kRingMask;
+    atomicAdd(reinterpret_cast<unsigned long long*>(ring + (size_t)fs * ring_stride + jl),
+              (unsigned long long)(long long)(int)(e & 0xFFFFFFFFu));
+    atomicOr(&fbits[fs * BW + (jl >> 5)], 1u << (jl & 31));
+  };
+  // The claim's ids (one per lane in qq) are delivered.  far: some event went
+  // to the ring, whose add must be complete first.  A claim may span steps.
+  auto delivered = [&](unsigned qq, unsigned c, bool far) {
     if (far) __builtin_amdgcn_s_waitcnt(0);
-    for (unsigned long long rem = c >= 64 ? ~0ull : (1ull << c) - 1; rem;) {   // a claim may span steps
+    for (unsigned long long rem = c >= 64 ? ~0ull : (1ull << c) - 1; rem;) {
       const unsigned st = (unsigned)__builtin_amdgcn_readlane((int)qq, __builtin_ctzll(rem)) >> 25 & 3u;
       const unsigned long long same = __ballot((qq >> 25 & 3u) == st) & rem;
       rem &= ~same;
@@ -513,21 +477,139 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
         __hip_atomic_fetch_add(&s_done[st], (unsigned)__popcll(same), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   };
+  // All events of ids [h, h + c) of the queue, c <= per: a group of 1 << ls
+  // lanes per id, kFew entries in flight per lane.  The fewest instructions
+  // for the few spikes of a quiet step.
+  auto deliver_few = [&](unsigned h, unsigned c) {
+    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];     // (lanes >= c unused)
+    const unsigned q = (unsigned)__shfl((int)qq, sub, 64);
+    const bool mine = sub < (int)c;
+    const unsigned id = mine ? q & 0x3FFFFu : 0u;
+    const unsigned* o = off + (size_t)id * (unsigned)(G + 1);
+    const long long rp = row_ptr[id];
+    const unsigned o0 = o[0], o1 = o[1];
+    __builtin_amdgcn_sched_barrier(0);                      // all three loads are out before the first is waited for
+    const long long ent = rp + o0 + sl_lane;
+    int len = mine ? (int)(o1 - o0) : 0;
+    const unsigned sn = __umul24((q >> 18) & 0x7Fu, B8);
+    if (sl_lane == 0) ev += (unsigned)len;
+    len -= sl_lane;                                         // this lane's entries: 0, L, 2L, ... < len
+    bool far = false;
+    for (int e = 0; __any(e < len); e += kFew << ls) {
+      unsigned long long v[kFew];
+      bool beyond = false;
+#pragma unroll
+      for (int u = 0; u < kFew; ++u) {
+        const bool ok = e + (u << ls) < len;
+        v[u] = 0;
+        if (ok) v[u] = pk[ent + e + (u << ls)];
+      }
+#pragma unroll
+      for (int u = 0; u < kFew; ++u) beyond |= add(v[u], sn);
+      if (__any(beyond)) {                                  // rare
+        far = true;
+#pragma unroll
+        for (int u = 0; u < kFew; ++u)
+          if ((unsigned)(v[u] >> 32) >= B8 + near_span) add_far(v[u], q >> 25);
+      }
+    }
+    delivered(qq, c, far);
+  };
+  // All events of ids [h, h + c), c <= 64: a lane per id finds its sub-row and
+  // cuts it into units of 1 << ls entries, listed in LDS; then the wavefront
+  // walks the units, 64 / L at a time (a slot), two groups of kSlots slots in
+  // flight.  One chain of dependent loads per claim and few idle lanes: the
+  // full microcircuit's bursts (600 to 3,000 spikes a step) went from 35 to 22 ns
+  // per spike with the units and to 19 with 12 wavefronts instead of 8.
+  auto deliver_many = [&](unsigned h, unsigned c) {
+    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];
+    const bool mine = lane < (int)c;
+    const unsigned id = mine ? qq & 0x3FFFFu : 0u;
+    const unsigned* o = off + (size_t)id * (unsigned)(G + 1);
+    const long long rp = row_ptr[id];
+    const unsigned o0 = o[0], o1 = o[1];
+    __builtin_amdgcn_sched_barrier(0);
+    const long long first = rp + o0;
+    const int len = mine ? (int)(o1 - o0) : 0;
+    ev += (unsigned)len;
+    const unsigned sn = __umul24((qq >> 18) & 0x7Fu, B8);
+    const int units = (len + (1 << ls) - 1) >> ls;
+    const int x = wave_incl(units), total = __builtin_amdgcn_readlane(x, 63), base = x - units;
+    uint4* const ul = s_units + wave * kUnits;              // this wavefront's
+    bool far = false;
+    for (int w0 = 0; w0 < total; w0 += kUnits) {
+      const int je = min(units, w0 + kUnits - base);
+      for (int j = max(0, w0 - base); j < je; ++j) {
+        const long long at = first + (j << ls);
+        ul[base + j - w0] = make_uint4((unsigned)at, (unsigned)(at >> 32), (unsigned)min(1 << ls, len - (j << ls)) | (qq >> 25) << 16, sn);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int nu = min(kUnits, total - w0);
+      const int groups = (nu + kSlots * per - 1) / (kSlots * per);
+      unsigned long long va[kSlots], vb[kSlots];
+      unsigned na[kSlots], nb[kSlots];
+      // (every lane loads, from a safe address if it has no entry, so that the
+      // wait for one group in flight leaves the other alone)
+      auto load = [&](unsigned long long* v, unsigned* sb, int grp) __attribute__((always_inline)) {
+        uint4 t[kSlots];
+        const int i0 = grp * kSlots * per + sub;
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u) t[u] = ul[min(i0 + u * per, kUnits - 1)];
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u) {
+          const bool ok = i0 + u * per < nu && sl_lane < (int)(t[u].z & 0xFFFFu);
+          v[u] = pk[ok ? (long long)((unsigned long long)t[u].y << 32 | t[u].x) + sl_lane : 0ll];
+          sb[u] = ok ? t[u].w : kNone;
+        }
+      };
+      auto process = [&](const unsigned long long* v, const unsigned* sb, int grp) __attribute__((always_inline)) {
+        bool beyond = false;
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u) beyond |= add(v[u], sb[u]);
+        if (__any(beyond)) {                                // rare
+          far = true;
+#pragma unroll
+          for (int u = 0; u < kSlots; ++u)
+            if ((int)sb[u] >= 0 && (unsigned)(v[u] >> 32) >= B8 + near_span)
+              add_far(v[u], ul[(grp * kSlots + u) * per + sub].z >> 16);
+        }
+      };
+      load(va, na, 0);
+      for (int grp = 0; grp < groups; grp += 2) {
+        if (grp + 1 < groups) load(vb, nb, grp + 1);
+        process(va, na, grp);
+        if (grp + 2 < groups) load(va, na, grp + 2);
+        if (grp + 1 < groups) process(vb, nb, grp + 1);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    delivered(qq, c, far);
+  };
   unsigned spins = 0;
   long long t_wait = 0;                       // wall clock at the first check of a wait (0: not waiting)
   long long tp_idle = kTime ? wall_clock64() : 0;
 
+  // The poller and the updates are the step's critical path: they issue ahead
+  // of the wavefronts that deliver (full microcircuit 4.27 -> 3.98 us per step,
+  // balanced 2.89 -> 2.58).
+  if (isP) __builtin_amdgcn_s_setprio(3);
   for (;;) {
     // ---- update: input of step n into I, spike decision and record of step
     //      n+1, once every event of the steps before n is in ---------------------
+    bool limited = false;                     // claim only ids before limit (but see below)
+    unsigned limit = 0;
     if (isU && uit < steps) {
       const long long n = n0 + uit;
       bool ready = uit == 0;
       if (!ready && uni(lds_acq(&s_listed)) >= uit) {
         const int k = (int)((n - 1) & 3);
+        limited = true;
+        limit = uni(s_endq[k]);
         ready = uni(lds_acq(&s_done[k]) - s_end[k]) == 0;
       }
       if (ready) {
+        __builtin_amdgcn_s_setprio(3);
         long long tp = 0;
         if (kTime) { tp = wall_clock64(); ph[2] += tp - tp_idle; }
         absorb(n, un);
@@ -546,6 +628,7 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
         }
         if (kTime) { tp_idle = wall_clock64(); ph[5] += tp_idle - tp; }
         t_wait = 0;
+        if (!isP) __builtin_amdgcn_s_setprio(0);
         continue;
       }
     }
@@ -559,69 +642,101 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
       const unsigned long long* recs = flags + window_word0(G, rslot, 0);
       const unsigned qtag = (unsigned)pn << 18 | (unsigned)(n & kRingMask) << 25;
       const unsigned tail0 = tail;
-      const volatile unsigned* done = s_done;   // ids delivered by now (the queue's room)
       unsigned long long w0[kPoll];
 #pragma unroll
       for (int k = 0; k < kPoll; ++k) w0[k] = ((todo >> k) & 1u) ? ld_dev(&recs[(lane + 64 * k) * kWord0Stride]) : 0ull;
-      const unsigned gone = done[0] + done[1] + done[2] + done[3];
-      unsigned busy = 0;                        // the k in which some record holds spikes
+      const unsigned gone = lds_rlx(&s_done[0]) + lds_rlx(&s_done[1]) + lds_rlx(&s_done[2]) + lds_rlx(&s_done[3]);   // ids delivered by now (the queue's room)
+      // records of up to four spikes: their ids are in word 0
+      unsigned few = 0, many = 0, cf = 0;       // the k of this lane's records by size; ids of the short ones
 #pragma unroll
       for (int k = 0; k < kPoll; ++k) {
-        const bool seen = ((todo >> k) & 1u) && (w0[k] >> 48) == t16p;
-        const bool some = seen && ((w0[k] >> 36) & 0xFFFu) != 0;
-        if (seen && !some) todo &= ~(1u << k);  // an empty record
-        if (__any(some)) busy |= 1u << k;
+        const unsigned hi = (unsigned)(w0[k] >> 32), c = (hi >> 4) & 0xFFFu;
+        if (((todo >> k) & 1u) && (hi >> 16) == t16p) {
+          if (c <= (unsigned)kW0Ids) { few |= 1u << k; cf += c; }
+          else many |= 1u << k;
+        }
       }
-#pragma unroll 1
-      for (; busy; busy &= busy - 1) {
-        const int k = __builtin_ctz(busy);
-        unsigned long long w = w0[0];
-        long long first = pbs[0];
-#pragma unroll
-        for (int u = 1; u < kPoll; ++u) {
-          w = (u == k) ? w0[u] : w;
-          first = (u == k) ? pbs[u] : first;
-        }
-        const int c = (((todo >> k) & 1u) && (w >> 48) == t16p) ? (int)((w >> 36) & 0xFFFu) : 0;
-        bool ok = c > 0;
-        const bool maps = c > kW0Ids;
-        unsigned long long wk[kMapWords];
-        const bool any_maps = __any(maps);
-        if (any_maps) {
-          const unsigned long long* mw = flags + window_map(G, rslot, lane + 64 * k);
-          const unsigned long long tag = (unsigned long long)t16p << 48;
-#pragma unroll
-          for (int L = 0; L < kMapWords; ++L) wk[L] = (maps && ((w >> L) & 1ull)) ? ld_dev(&mw[L]) : tag;
-#pragma unroll
-          for (int L = 0; L < kMapWords; ++L) ok &= (wk[L] >> 48) == t16p;
-        }
-        const int x = wave_incl(ok ? c : 0);
-        ok = ok && x <= (int)(qcap - (tail - gone));   // room in the queue
+      if (!__any(cf != 0)) {
+        todo &= ~few;                           // nothing but empty records
+      } else {
+        const int x = wave_incl((int)cf);
+        const bool ok = x <= (int)(qcap - (tail - gone));   // room in the queue: the accepted lanes are a prefix
         if (ok) {
-          todo &= ~(1u << k);
-          unsigned o = tail + (unsigned)(x - c);
-          const unsigned b = (unsigned)first | qtag;   // ids < 2^18, and first + local index too: no carry
-          if (!maps) {
-            for (int e = 0; e < c; ++e) s_q[o++ & (kQueue - 1)] = b + (unsigned)((w >> (9 * e)) & 0x1FFull);
-          } else {
+          todo &= ~few;
+          unsigned o = tail + (unsigned)x - cf;
 #pragma unroll
-            for (int L = 0; L < kMapWords; ++L)
-              for (unsigned long long mm = wk[L] & ((1ull << kMapBits) - 1); mm; mm &= mm - 1)
-                s_q[o++ & (kQueue - 1)] = b + (unsigned)(kMapBits * L + __builtin_ctzll(mm));
+          for (int k = 0; k < kPoll; ++k) {
+            const unsigned c = ((few >> k) & 1u) ? ((unsigned)(w0[k] >> 36) & 0xFFFu) : 0u;
+            const unsigned b = (unsigned)((lane + 64 * k) * B) | qtag;   // ids < 2^18, with a local index too: no carry
+#pragma unroll
+            for (int e = 0; e < kW0Ids; ++e)
+              if ((unsigned)e < c) s_q[(o + (unsigned)e) & (kQueue - 1)] = b + ((unsigned)(w0[k] >> (9 * e)) & 0x1FFu);
+            o += c;
           }
         }
-        // the accepted lanes are a prefix of those with complete records
         const unsigned long long acc_m = __ballot(ok);
         if (acc_m) tail += (unsigned)__builtin_amdgcn_readlane(x, 63 - __builtin_clzll(acc_m));
+        if (lane == 0) lds_rel(&s_tail, tail);
+      }
+      // longer records: 16 lanes read the bitmap words of one, sixteen records
+      // in flight; a lane puts in the ids of its word
+      if (__any(many != 0)) {
+#pragma unroll 1
+        for (int k = 0; k < kPoll; ++k) {
+          unsigned long long w = w0[0];
+#pragma unroll
+          for (int u = 1; u < kPoll; ++u) w = (u == k) ? w0[u] : w;
+          unsigned long long left = __ballot((many >> k) & 1u);
+          const int L = lane & 15, rr = lane >> 4;
+          while (left) {
+            constexpr int kBatch = 4;
+            unsigned long long wk[kBatch];
+            int own[kBatch];                    // the lane that polls this group's record (-1: none)
+            bool need[kBatch];
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+              own[q] = -1;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int l = left ? __builtin_ctzll(left) : -1;
+                left &= left - 1;               // (0 stays 0)
+                own[q] = (rr == e) ? l : own[q];
+              }
+              const unsigned long long wr = __shfl(w, own[q] & 63, 64);
+              need[q] = own[q] >= 0 && L < kMapWords && ((wr >> L) & 1ull);
+              wk[q] = 0;
+              if (need[q]) wk[q] = ld_dev(&flags[window_map(G, rslot, own[q] + 64 * k) + L]);
+            }
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+              const unsigned long long bad = __ballot(need[q] && (unsigned)(wk[q] >> 48) != t16p);
+              const bool good = own[q] >= 0 && ((bad >> (lane & 48)) & 0xFFFFull) == 0;
+              unsigned long long mm = (good && need[q]) ? wk[q] & ((1ull << kMapBits) - 1) : 0ull;
+              const int x = wave_incl(__popcll(mm)), xr = __shfl(x, lane | 15, 64);   // up to the end of the record
+              const bool ok = good && xr <= (int)(qcap - (tail - gone));
+              if (ok) {
+                unsigned o = tail + (unsigned)(x - __popcll(mm));
+                const unsigned b = ((unsigned)((own[q] + 64 * k) * B) | qtag) + (unsigned)(kMapBits * L);
+                for (; mm; mm &= mm - 1) s_q[o++ & (kQueue - 1)] = b + (unsigned)__builtin_ctzll(mm);
+              }
+              const unsigned long long acc_m = __ballot(ok);
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if ((acc_m >> (16 * e)) & 1ull && lane == __builtin_amdgcn_readlane(own[q], 16 * e)) todo &= ~(1u << k);
+              if (acc_m) tail += (unsigned)__builtin_amdgcn_readlane(x, 63 - __builtin_clzll(acc_m));
+            }
+            if (lane == 0) lds_rel(&s_tail, tail);
+          }
+        }
       }
       progress = tail != tail0;
       const bool complete = !__any(todo != 0);
-      if (lane == 0 && progress) lds_rel(&s_tail, tail);
       if (complete) {
         if (lane == 0) {
           const int k = (int)(n & 3);
           // the ids of this step: all put in so far less those of the other steps
           s_end[k] = tail - s_end[(k + 1) & 3] - s_end[(k + 2) & 3] - s_end[(k + 3) & 3];
+          s_endq[k] = tail;
           lds_rel(&s_listed, pit + 1);
         }
         progress = true;
@@ -636,12 +751,16 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (delivers || (pit == steps && uit >= (isU ? steps : 0))) {
       unsigned h = 0, c = 0;
       {
-        const unsigned t = uni(lds_acq(&s_tail));
-        h = uni(*(volatile unsigned*)&s_head);    // (may be past t by now)
+        unsigned t = uni(lds_acq(&s_tail));
+        // later steps' ids are not what an update waits for: it leaves them to
+        // the other wavefronts unless many pile up (a burst)
+        if (limited && (int)(t - limit) <= nw * per) t = limit;
+        h = uni(lds_rlx(&s_head));    // (may be past t by now)
         if ((int)(t - h) > 0) {
           if (lane == 0) {
             while ((int)(t - h) > 0) {
-              const unsigned want = min(t - h, (unsigned)(t - h > (unsigned)(nw * per) ? kRounds * per : per));
+              // (a short queue is shared out in single rounds, a long one evenly)
+              const unsigned want = min(t - h, (unsigned)min(64, max(per, (int)(t - h) / nw)));
               if (__hip_atomic_compare_exchange_strong(&s_head, &h, h + want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_WORKGROUP)) {
                 c = want;
@@ -655,8 +774,8 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
       }
       if (c > 0) {
         const long long tq = kTime ? wall_clock64() : 0;
-        if (c <= (unsigned)per) deliver(std::integral_constant<int, 1>(), std::integral_constant<int, kPassesShort>(), h, c);
-        else deliver(std::integral_constant<int, kRounds>(), std::integral_constant<int, kPasses>(), h, c);
+        if (c <= (unsigned)per) deliver_few(h, c);
+        else deliver_many(h, c);
         if (kTime) { const long long t = wall_clock64(); ph[4] += t - tq; tp_idle += t - tq; }
         t_wait = 0;
         continue;
@@ -665,9 +784,9 @@ __global__ __launch_bounds__(kPersistMaxBlock) void k_persist(DevNet p, PersistA
     if (progress) { t_wait = 0; continue; }
     // ---- nothing to do now -------------------------------------------------------
     if ((!isU || uit == steps) && (!isP || pit == steps) && uni(lds_acq(&s_listed)) == steps &&
-        uni(*(volatile unsigned*)&s_head - *(volatile unsigned*)&s_tail) == 0)
+        uni(lds_rlx(&s_head) - lds_rlx(&s_tail)) == 0)
       break;
-    if (uni(*(volatile int*)&s_abort)) break;
+    if (uni(lds_rlx(&s_abort))) break;
     if (!isU) __builtin_amdgcn_s_sleep(1);
     // (a wavefront that only delivers may rightly idle for long)
     if ((isP || isU) && (++spins & 255u) == 0u) {   // the wall clock is read every 256 rounds only
@@ -874,7 +993,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_rows(const int64_t* row_ptr
 size_t persist_lds_bytes(int G, int B, int DL) {
   (void)G;
   const int BW = (B + 31) / 32;
-  return (size_t)DL * B * 8 + (size_t)128 * BW * 4 + (size_t)kQueue * 4;
+  return (size_t)DL * B * 8 + (size_t)128 * BW * 4 + (size_t)kQueue * 4 + (size_t)(kPersistThreads / 64) * kUnits * 16;
 }
 
 // The instances of k_persist (recording, timing, poll width); shapes are
