@@ -213,10 +213,12 @@ struct mc_net {
   int launches_timed = 0;
   int64_t steps_timed = 0;
   hipStream_t aux = nullptr;           // read-back of the raster beside the simulation stream
-  int2* d_pack = nullptr;              // raster prefixes packed for one read-back
-  int64_t pack_cap = 0;
-  long long* d_pack_off = nullptr;     // [n_wg+1]
-  int64_t pack_off_cap = 0;
+  // read-back of the raster (drain)
+  int64_t* d_inst_off = nullptr;       // [n_inst+1] dense
+  int* d_rwork = nullptr;              // scratch of a long read-back
+  int64_t rwork_cap = 0;
+  long long* h_spk = nullptr;          // pinned: 3 header words, steps, ids
+  int64_t spk_cap = 0;                 // spikes it holds
   void* h_stage = nullptr;             // pinned staging of the adjoint's work lists
   size_t stage_bytes = 0;
   double last_ms = 0.0;
@@ -319,8 +321,9 @@ void release_all(mc_net* n) {
   if (n->ev_mid) { (void)hipEventDestroy(n->ev_mid); n->ev_mid = nullptr; }
   for (hipEvent_t e : n->ev_launch) (void)hipEventDestroy(e);
   n->ev_launch.clear();
-  dev_free(n->alloc, n->d_pack); dev_free(n->alloc, n->d_pack_off);
-  n->pack_cap = 0; n->pack_off_cap = 0;
+  dev_free(n->alloc, n->d_inst_off); dev_free(n->alloc, n->d_rwork);
+  n->rwork_cap = 0;
+  if (n->h_spk) { (void)hipHostFree(n->h_spk); n->h_spk = nullptr; n->spk_cap = 0; }
   if (n->h_stage) { (void)hipHostFree(n->h_stage); n->h_stage = nullptr; n->stage_bytes = 0; }
   if (n->aux) { (void)hipStreamDestroy(n->aux); n->aux = nullptr; }
   if (n->own_stream && n->stream) { (void)hipStreamDestroy(n->stream); n->stream = nullptr; }
@@ -332,20 +335,45 @@ int64_t spike_bound(int64_t neurons, int64_t steps, int ref) {
   return neurons * ((steps + ref) / (ref + 1));
 }
 
-// Copies the private raster segments to the host list (sorted by step, id)
-// and empties them.  Waits for `upto` (an event on the simulation stream) if
-// given, else for the whole simulation stream; the read-back itself runs on
-// the second stream, so work queued after `upto` keeps running.
+// Pinned memory for a read-back of `spikes` spikes.
+int reserve_spikes(mc_net* n, int64_t spikes) {
+  if (n->h_spk && n->spk_cap >= spikes) return MC_OK;
+  if (n->h_spk) { (void)hipHostFree(n->h_spk); n->h_spk = nullptr; n->spk_cap = 0; }
+  HIP_TRY(hipHostMalloc((void**)&n->h_spk, sizeof(long long) * 4 + sizeof(int) * 2 * (size_t)spikes, hipHostMallocDefault));
+  n->spk_cap = spikes;
+  return MC_OK;
+}
+
+// Moves the spikes of the private raster segments to the host list (sorted by
+// step, id) and empties the segments.  Waits for `upto` (an event on the
+// simulation stream) if given, and the read-back then runs on the second
+// stream, so work queued after `upto` keeps running; else for the whole
+// simulation stream.
 int drain(mc_net* n, hipEvent_t upto = nullptr) {
   if (!n->d_raster) return MC_OK;
-  if (upto) HIP_TRY(hipEventSynchronize(upto));
-  else HIP_TRY(hipStreamSynchronize(n->stream));
-  hipStream_t s = n->aux;
-  unsigned ovf = 0;
-  std::vector<long long> cnt((size_t)n->n_wg);
-  HIP_TRY(hipMemcpyAsync(&ovf, n->d_overflow, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(cnt.data(), n->d_raster_cnt, sizeof(long long) * n->n_wg, hipMemcpyDeviceToHost, s));
+  hipStream_t s = upto ? n->aux : n->stream;
+  if (n->steps_since_drain == 0) {             // nothing simulated since the last one
+    if (!upto) HIP_TRY(hipStreamSynchronize(s));
+    return MC_OK;
+  }
+  int rc;
+  if ((rc = reserve_spikes(n, std::max<int64_t>(n->spk_cap, kRasterSmall))) != MC_OK) return rc;
+  if (upto) HIP_TRY(hipStreamWaitEvent(s, upto, 0));
+  RasterArgs a{};
+  auto outputs = [&] {
+    a.head = n->h_spk;
+    a.out_step = reinterpret_cast<int*>(n->h_spk + 4);
+    a.out_id = a.out_step + n->spk_cap;
+  };
+  a.raster = n->d_raster; a.cap = n->raster_cap; a.cnt = n->d_raster_cnt; a.n_seg = n->n_wg;
+  a.lo = (int)(n->step - n->steps_since_drain);
+  a.span = (int)n->steps_since_drain;
+  a.overflow = n->d_overflow; a.inst_pad = n->d_inst_base; a.inst_off = n->d_inst_off; a.n_inst = n->h.n_inst;
+  outputs();
+  HIP_TRY(launch_raster_small(a, s));
   HIP_TRY(hipStreamSynchronize(s));
+  const long long total = n->h_spk[0];
+  const unsigned ovf = (unsigned)n->h_spk[1];
   if (ovf & kErrWaitTimeout) {
     n->failed = true;
     return set_error(MC_ERR_TIMEOUT, "persistent kernel: a workgroup waited more than " + std::to_string(kWaitSeconds) +
@@ -355,55 +383,29 @@ int drain(mc_net* n, hipEvent_t upto = nullptr) {
     n->failed = true;
     return set_error(MC_ERR_STATE, "raster segment overflow (internal capacity error)");
   }
-  std::vector<long long> seg_off((size_t)n->n_wg + 1, 0);
-  for (int g = 0; g < n->n_wg; ++g) seg_off[g + 1] = seg_off[g] + cnt[g];
-  const long long total = seg_off[n->n_wg];
-  std::vector<int2> buf((size_t)total);
-  if (total > 0) {
-    // the used prefixes packed on the device, then one copy
-    int rc;
-    if (n->pack_off_cap < n->n_wg + 1) {
-      dev_free(n->alloc, n->d_pack_off);
-      n->pack_off_cap = 0;
-      if ((rc = dev_alloc(n->alloc, &n->d_pack_off, (size_t)n->n_wg + 1)) != MC_OK) return rc;
-      n->pack_off_cap = n->n_wg + 1;
+  if (n->h_spk[2] == 0) {                      // more than one workgroup reads back
+    if (total > 2147483647LL) return set_error(MC_ERR_RANGE, "more than 2^31 spikes between two read-backs");
+    const int64_t span = n->steps_since_drain;
+    // (room to spare: the spikes of equal spans vary with the activity)
+    if (total > n->spk_cap && (rc = reserve_spikes(n, total + total / 2)) != MC_OK) return rc;
+    outputs();
+    const int64_t need = 3 * (span + 64) + total;
+    if (n->rwork_cap < need) {
+      dev_free(n->alloc, n->d_rwork);
+      n->rwork_cap = 0;
+      if ((rc = dev_alloc(n->alloc, &n->d_rwork, (size_t)(need + total / 2))) != MC_OK) return rc;
+      n->rwork_cap = need + total / 2;
     }
-    if (n->pack_cap < total) {
-      dev_free(n->alloc, n->d_pack);
-      n->pack_cap = 0;
-      if ((rc = dev_alloc(n->alloc, &n->d_pack, (size_t)total)) != MC_OK) return rc;
-      n->pack_cap = total;
-    }
-    HIP_TRY(hipMemcpyAsync(n->d_pack_off, seg_off.data(), sizeof(long long) * (n->n_wg + 1), hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_raster_pack(n->d_raster, n->raster_cap, n->d_pack_off, n->n_wg, n->d_pack, s));
-    HIP_TRY(hipMemcpyAsync(buf.data(), n->d_pack, sizeof(int2) * total, hipMemcpyDeviceToHost, s));
+    int *hist = n->d_rwork, *off = hist + span + 64, *cursor = off + span + 64, *bucket = cursor + span + 64;
+    HIP_TRY(launch_raster_order(a, n->n_pad, hist, off, cursor, bucket, s));
+    HIP_TRY(hipStreamSynchronize(s));
   }
-  HIP_TRY(hipMemsetAsync(n->d_raster_cnt, 0, sizeof(long long) * n->n_wg, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  // Workgroup g's segment holds its own neurons, whose ids all exceed those
-  // of workgroups < g, by step; a stable counting sort by step over the
-  // segments in order groups a step's spikes by workgroup.  The persistent
-  // and step kernels write a step's ids in ascending order, the bucket
-  // kernel in any order: a step whose ids are not ascending is sorted.
-  if (total > 0) {
-    int smin = buf[0].x, smax = buf[0].x;
-    for (const int2& e : buf) { smin = std::min(smin, e.x); smax = std::max(smax, e.x); }
-    std::vector<size_t> pos((size_t)(smax - smin) + 2, 0);
-    for (const int2& e : buf) ++pos[(size_t)(e.x - smin) + 1];
-    for (size_t k = 1; k < pos.size(); ++k) pos[k] += pos[k - 1];
-    const std::vector<size_t> first(pos);
-    const size_t base = n->r_step.size();
-    n->r_step.resize(base + (size_t)total);
-    n->r_id.resize(base + (size_t)total);
-    for (const int2& e : buf) {
-      const size_t k = base + pos[(size_t)(e.x - smin)]++;
-      n->r_step[k] = e.x;
-      n->r_id[k] = (int32_t)n->dense_of(e.y);
-    }
-    for (size_t k = 0; k + 1 < first.size(); ++k) {
-      auto b = n->r_id.begin() + (std::ptrdiff_t)(base + first[k]), e = n->r_id.begin() + (std::ptrdiff_t)(base + first[k + 1]);
-      if (!std::is_sorted(b, e)) std::sort(b, e);
-    }
+  try {
+    n->r_step.insert(n->r_step.end(), a.out_step, a.out_step + total);
+    n->r_id.insert(n->r_id.end(), a.out_id, a.out_id + total);
+  } catch (const std::bad_alloc&) {
+    n->failed = true;
+    return set_error(MC_ERR_OOM, "host allocation of the spike list failed");
   }
   n->steps_since_drain = 0;
   return MC_OK;
@@ -918,6 +920,8 @@ int upload_network(mc_net* n) {
   if ((rc = dev_alloc(n->alloc, &n->d_inst_base, (size_t)h.n_inst + 1)) != MC_OK) return rc;
   if ((rc = dev_alloc(n->alloc, &n->d_ilist, (size_t)2 * P)) != MC_OK) return rc;
   if ((rc = dev_alloc(n->alloc, &n->d_icnt, (size_t)2 * h.n_inst)) != MC_OK) return rc;
+  if ((rc = dev_alloc(n->alloc, &n->d_inst_off, (size_t)h.n_inst + 1)) != MC_OK) return rc;
+  HIP_TRY(hipMemcpy(n->d_inst_off, h.inst_off.data(), sizeof(int64_t) * (h.n_inst + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(n->d_qinst, qinst.data(), sizeof(int32_t) * n->n_quads, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(n->d_inst_base, n->inst_off_pad.data(), sizeof(int64_t) * (h.n_inst + 1), hipMemcpyHostToDevice));
   HIP_TRY(hipMemset(n->d_icnt, 0, sizeof(int) * 2 * h.n_inst));

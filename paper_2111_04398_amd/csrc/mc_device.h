@@ -244,7 +244,25 @@ hipError_t launch_weights(int32_t* wq, const void* src, int mode, double eta, lo
 // ConnBuilder; grid: workgroups of 256 threads; s: the stream it uses).
 struct ConnBuilder;
 ConnBuilder* new_device_conn(int grid, hipStream_t s);
-// Raster segments' used prefixes -> one contiguous array (off: [n_seg+1] exclusive prefix of the counts).
-hipError_t launch_raster_pack(const int2* raster, long long cap, const long long* off, int n_seg, int2* out,
-                              hipStream_t s);
+// Read-back of the raster segments, sorted by (step, id) (mc_raster.hip).
+struct RasterArgs {
+  const int2* raster;          // [n_seg][cap] (step, padded id), by step inside a segment
+  long long cap;
+  long long* cnt;              // [n_seg] entries of every segment; emptied once they have been read
+  int n_seg;
+  int lo, span;                // the segments hold steps lo .. lo + span - 1
+  const unsigned* overflow;    // error bits of the simulation kernels
+  const int64_t* inst_pad;     // [n_inst+1] first padded id of every instance
+  const int64_t* inst_off;     // [n_inst+1] first dense id
+  int n_inst;
+  int* out_step;               // pinned host memory
+  int* out_id;
+  long long* head;             // pinned, 3 words (see k_raster_small)
+};
+constexpr int kRasterSmall = 2048;        // spikes read back by one workgroup
+hipError_t launch_raster_small(const RasterArgs& a, hipStream_t s);
+// Any number of spikes: hist [span], off [span+1],
+// cursor [span] and bucket [spikes] are scratch.
+hipError_t launch_raster_order(const RasterArgs& a, long long n_pad, int* hist, int* off, int* cursor, int* bucket,
+                               hipStream_t s);
 }  // namespace mc

@@ -1,0 +1,49 @@
+"""The raster's read-back (ordered on the device) against the oracle, at the
+edges of its ways: no spike, one workgroup's sort up to 2,048 spikes, beyond
+that a step's spikes by rank (up to 256) and through the id bitmap (one and
+several passes of 2^18 ids)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2111_04398_amd import mc, workloads
+from test_gpu_parity import assert_same
+from test_oracle_dynamics import lone_neuron
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("scheme,block,npw", [(0, 256, 256), (1, 512, 0), (3, 256, 0)])
+@pytest.mark.parametrize("steps", [1, 2, 300])
+def test_read_back_after_every_span(scheme, block, npw, steps):
+    """Spans of 0 to ~2,000 spikes and of several thousand, read after each and all at once."""
+    w = workloads.balanced()
+    net, whole, o = mc.Network(w), mc.Network(w), oracle.Oracle(w.to_dict())
+    for n in (net, whole):
+        n.set_launch(scheme=scheme, block=block, neurons_per_wg=npw, steps_per_graph=100)
+    got = []
+    for k in range(4):
+        net.simulate(steps)
+        got.append(net.spikes(k * steps, (k + 1) * steps))
+    whole.simulate(4 * steps)
+    o.run(4 * steps)
+    os_, oi = o.raster()
+    assert np.array_equal(np.concatenate([g[0] for g in got]), os_)
+    assert np.array_equal(np.concatenate([g[1] for g in got]), oi)
+    assert_same(whole, o, ring_depth=4, what="one read-back")
+
+
+@pytest.mark.parametrize("n", [255, 2048, 2049, 300000])
+def test_every_neuron_fires_at_once(n):
+    """All neurons of an unconnected population fire in the same steps: total and per-step
+    counts on both sides of the limits, ids beyond one bitmap pass."""
+    w = lone_neuron(i_e=1000.0).replace(pop_size=[n])
+    net = mc.Network(w)
+    net.set_launch(scheme=0, block=256, neurons_per_wg=256, steps_per_graph=0)
+    net.simulate(200)
+    s, i = net.spikes()
+    one = mc.Network(lone_neuron(i_e=1000.0))
+    one.simulate(200)
+    ref = one.spikes()[0]
+    assert len(ref) >= 1 and len(s) == n * len(ref)
+    assert np.array_equal(s, np.repeat(ref, n)) and np.array_equal(i, np.tile(np.arange(n, dtype=np.int32), len(ref)))
