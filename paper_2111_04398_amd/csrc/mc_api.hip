@@ -219,6 +219,7 @@ struct mc_net {
   int64_t rwork_cap = 0;
   long long* h_spk = nullptr;          // pinned: 3 header words, steps, ids
   int64_t spk_cap = 0;                 // spikes it holds
+  unsigned* d_adj_rb = nullptr;        // the adjoint's target ranges [n_pad][kAdjRanges+1], made at its first use
   void* h_stage = nullptr;             // pinned staging of the adjoint's work lists
   size_t stage_bytes = 0;
   double last_ms = 0.0;
@@ -321,7 +322,7 @@ void release_all(mc_net* n) {
   if (n->ev_mid) { (void)hipEventDestroy(n->ev_mid); n->ev_mid = nullptr; }
   for (hipEvent_t e : n->ev_launch) (void)hipEventDestroy(e);
   n->ev_launch.clear();
-  dev_free(n->alloc, n->d_inst_off); dev_free(n->alloc, n->d_rwork);
+  dev_free(n->alloc, n->d_inst_off); dev_free(n->alloc, n->d_rwork); dev_free(n->alloc, n->d_adj_rb);
   n->rwork_cap = 0;
   if (n->h_spk) { (void)hipHostFree(n->h_spk); n->h_spk = nullptr; n->spk_cap = 0; }
   if (n->h_stage) { (void)hipHostFree(n->h_stage); n->h_stage = nullptr; n->stage_bytes = 0; }
@@ -1777,7 +1778,7 @@ int mc_get_persist_shape(mc_net* n, int32_t* G, int32_t* B, int32_t* DL) {
 // Largest input record an adjoint makes by default (8 B per neuron-step).
 constexpr double kRecordBudget = 16.0 * 1024 * 1024 * 1024;
 
-int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) {
+static int run_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) {
   if (!device_ready(n)) return set_error(MC_ERR_STATE, "handle is host-only, failed or NULL");
   if (!a || !grad || !loss) return set_error(MC_ERR_INVALID_ARG, "NULL config, gradient or loss pointer");
   if (a->struct_size != sizeof(mc_adjoint_config)) return set_error(MC_ERR_INVALID_ARG, "mc_adjoint_config.struct_size mismatch");
@@ -1828,6 +1829,10 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
   if ((rc = B.alloc(&seg_count, (size_t)nseg)) != MC_OK) return rc;
   if ((rc = B.alloc(&mismatch, 1)) != MC_OK) return rc;
   loss_part = carry + 2 * st;
+  if (adj_gather_ranged(st) && !n->d_adj_rb &&
+      dev_alloc(n->alloc, &n->d_adj_rb, (size_t)n->n_pad * (kAdjRanges + 1)) == MC_OK)
+    HIP_TRY(launch_adj_bounds(n->d_row_ptr, n->d_tgt, n->n_pad, n->d_adj_rb, n->stream));
+  const bool ranged = n->d_adj_rb != nullptr;  // (without the memory for it, the plain gather)
   HIP_TRY(hipMemsetAsync(carry, 0, sizeof(double) * 3 * st, n->stream));
   HIP_TRY(hipMemsetAsync(seg_count, 0, sizeof(unsigned long long) * nseg, n->stream));
   HIP_TRY(hipMemsetAsync(mismatch, 0, sizeof(unsigned), n->stream));
@@ -1874,7 +1879,6 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
     sg.a = s0; sg.len = (int)len; sg.R = R; sg.c = c; sg.ystar = ystar;
     sg.ck_y = ck_y + k * st; sg.ck_I = ck_I + k * st; sg.ck_r = ck_r + k * st;
     sg.xseg = record ? xrec + (size_t)(s0 - n0) * st : xseg;
-    sg.x_has_drive = record ? 1 : 0;
     sg.rec_y = rec_y; sg.rec_t = rec_t; sg.li_ring = li_ring;
     sg.carry_ly = carry; sg.carry_li = carry + st; sg.loss_part = loss_part; sg.spike_count = seg_count + k;
     return sg;
@@ -1902,7 +1906,7 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
   // the host builds segment k-1's lists while the device runs segment k.
   struct SegLists {
     size_t dl_f, dl_c, vf_f, vf_c, ga_f, ga_c;   // raster ranges
-    size_t o_dl, o_first, o_vf, o_srcs, o_gfirst, o_times;   // byte offsets in the staging / device arena
+    size_t o_dl, o_first, o_vf, o_srcs, o_gfirst, o_times, o_end;   // byte offsets in the staging / device arena
   };
   std::vector<SegLists> L((size_t)nseg);
   size_t bytes = 0;
@@ -1918,8 +1922,9 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
     q.o_first = take(sizeof(long long) * (q.dl_c + 1));
     q.o_vf = take(sizeof(int2) * q.vf_c);
     q.o_srcs = take(sizeof(int4) * q.ga_c);
-    q.o_gfirst = take(sizeof(long long) * (q.ga_c + 1));
+    q.o_gfirst = take(ranged ? 0 : sizeof(long long) * (q.ga_c + 1));
     q.o_times = take(sizeof(int) * q.ga_c);
+    q.o_end = bytes;
   }
   unsigned char* d_lists = nullptr;
   if ((rc = B.alloc(&d_lists, bytes)) != MC_OK) return rc;
@@ -1930,7 +1935,10 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
   }
   unsigned char* h = static_cast<unsigned char*>(n->h_stage);
   std::vector<unsigned long long> want_count((size_t)nseg);
-  std::vector<unsigned long long> keys;
+  // the window's spikes, contiguous; and the place of every source in the
+  // gather list of the segment at hand
+  const std::vector<int32_t> w_step(n->r_step.begin() + lo, n->r_step.begin() + hi), w_id(n->r_id.begin() + lo, n->r_id.begin() + hi);
+  std::vector<int32_t> seg_of((size_t)n->h.N, -1), place((size_t)n->h.N, 0), at;
   for (int64_t k = nseg - 1; k >= 0; --k) {
     const int64_t s0 = n0 + k * K, len = std::min(K, S - k * K);
     const SegLists& q = L[(size_t)k];
@@ -1940,21 +1948,21 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
       int2* dl = reinterpret_cast<int2*>(h + q.o_dl);
       long long* first = reinterpret_cast<long long*>(h + q.o_first);
       for (size_t z = 0; z < q.dl_c; ++z) {
-        const int64_t dense = n->r_id[q.dl_f + z];
+        const int64_t dense = w_id[q.dl_f - (size_t)lo + z];
         const int64_t rl = n->h.row_ptr[dense + 1] - n->h.row_ptr[dense];
-        dl[z] = make_int2(n->r_step[q.dl_f + z], (int)n->pad_of(dense));
+        dl[z] = make_int2(w_step[q.dl_f - (size_t)lo + z], (int)n->pad_of(dense));
         first[z] = dl_chunks;
         dl_chunks += (rl + kReplayChunkHost - 1) / kReplayChunkHost;
       }
       first[q.dl_c] = dl_chunks;
     }
     int2* vf = reinterpret_cast<int2*>(h + q.o_vf);
-    for (size_t z = 0; z < q.vf_c; ++z) vf[z] = make_int2(n->r_step[q.vf_f + z], (int)n->pad_of(n->r_id[q.vf_f + z]));
+    for (size_t z = 0; z < q.vf_c; ++z) vf[z] = make_int2(w_step[q.vf_f - (size_t)lo + z], (int)n->pad_of(w_id[q.vf_f - (size_t)lo + z]));
     want_count[(size_t)k] = q.vf_c;
     // dl, first and vf lie before the gather lists in the arena: one copy
     HIP_TRY(hipMemcpyAsync(d_lists + q.o_dl, h + q.o_dl, q.o_srcs - q.o_dl, hipMemcpyHostToDevice, n->stream));
     if (!record) {
-      HIP_TRY(launch_adj_seed(xseg, ck_ring + k * ring_elems, st, s0, (int)(len + 101), n->stream));
+      HIP_TRY(launch_adj_seed(p, xseg, ck_ring + k * ring_elems, s0, (int)len, (int)(len + 101), n->stream));
       if (q.dl_c)
         HIP_TRY(launch_replay(reinterpret_cast<const int2*>(d_lists + q.o_dl),
                               reinterpret_cast<const long long*>(d_lists + q.o_first), (int)q.dl_c, dl_chunks,
@@ -1963,38 +1971,51 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
     if (!(record && k == nseg - 1)) HIP_TRY(launch_adj_segment(p, seg_args(k), n->stream));
     HIP_TRY(launch_adj_verify(reinterpret_cast<const int2*>(d_lists + q.o_vf), (int)q.vf_c, rec_t, st, s0, mismatch,
                               n->stream));
-    // gather: group by source (ascending), times decreasing; per source its chunk range
-    keys.resize(q.ga_c);
-    for (size_t z = 0; z < q.ga_c; ++z)
-      keys[z] = (unsigned long long)(uint32_t)n->r_id[q.ga_f + z] << 32 | (uint32_t)(0x7FFFFFFF - n->r_step[q.ga_f + z]);
-    std::sort(keys.begin(), keys.end());
+    // gather: group by source (in order of their first spike), times
+    // decreasing; per source its chunk range.  Counted, not sorted: the host
+    // builds a segment's lists while the device runs the one before.
+    if (q.ga_c == 0) continue;
     int4* srcs = reinterpret_cast<int4*>(h + q.o_srcs);
-    long long* gfirst = reinterpret_cast<long long*>(h + q.o_gfirst);
     int* times = reinterpret_cast<int*>(h + q.o_times);
-    long long chunks = 0;
+    const int32_t* g_id = w_id.data() + (q.ga_f - (size_t)lo);
+    const int32_t* g_step = w_step.data() + (q.ga_f - (size_t)lo);
     int nsrc = 0;
-    for (size_t z = 0; z < q.ga_c;) {
-      size_t e = z;
-      const uint32_t src = (uint32_t)(keys[z] >> 32);
-      while (e < q.ga_c && (uint32_t)(keys[e] >> 32) == src) ++e;
-      const int64_t rl = n->h.row_ptr[src + 1] - n->h.row_ptr[src];
-      for (size_t y = z; y < e; ++y) times[y] = 0x7FFFFFFF - (int)(uint32_t)(keys[y] & 0xFFFFFFFFu);
-      srcs[nsrc] = make_int4((int)n->pad_of(src), (int)z, (int)(e - z), 0);
-      gfirst[nsrc] = chunks;
-      chunks += (rl + kGatherChunkHost - 1) / kGatherChunkHost;
-      ++nsrc;
-      z = e;
+    for (size_t z = 0; z < q.ga_c; ++z) {
+      const int32_t src = g_id[z];
+      if (seg_of[src] != (int32_t)k) {
+        seg_of[src] = (int32_t)k;
+        place[src] = nsrc;
+        srcs[nsrc++] = make_int4(src, 0, 0, 0);
+      }
+      ++srcs[place[src]].z;
     }
-    gfirst[nsrc] = chunks;
-    if (nsrc == 0) continue;
-    HIP_TRY(hipMemcpyAsync(d_lists + q.o_srcs, h + q.o_srcs, sizeof(int4) * nsrc, hipMemcpyHostToDevice, n->stream));
-    HIP_TRY(hipMemcpyAsync(d_lists + q.o_gfirst, h + q.o_gfirst, sizeof(long long) * (nsrc + 1), hipMemcpyHostToDevice,
-                           n->stream));
-    HIP_TRY(hipMemcpyAsync(d_lists + q.o_times, h + q.o_times, sizeof(int) * q.ga_c, hipMemcpyHostToDevice, n->stream));
-    HIP_TRY(launch_adj_gather(reinterpret_cast<const int4*>(d_lists + q.o_srcs),
-                              reinterpret_cast<const long long*>(d_lists + q.o_gfirst), nsrc, chunks,
-                              reinterpret_cast<const int*>(d_lists + q.o_times), n->d_row_ptr, n->d_tgt, n->d_dly,
-                              li_ring, st, R, n0 + S - 1, grad, fp32, grid, n->stream));
+    at.resize((size_t)nsrc);
+    int before = 0;
+    for (int z = 0; z < nsrc; ++z) {
+      srcs[z].y = before;
+      before += srcs[z].z;
+      at[(size_t)z] = before;
+    }
+    for (size_t z = 0; z < q.ga_c; ++z) times[--at[(size_t)place[g_id[z]]]] = g_step[z];   // the earliest last
+    long long* gfirst = reinterpret_cast<long long*>(h + q.o_gfirst);
+    long long chunks = 0;
+    for (int z = 0; z < nsrc; ++z) {
+      const int32_t src = srcs[z].x;
+      srcs[z].x = (int)n->pad_of(src);
+      if (ranged) continue;
+      gfirst[z] = chunks;
+      chunks += (n->h.row_ptr[src + 1] - n->h.row_ptr[src] + kGatherChunkHost - 1) / kGatherChunkHost;
+    }
+    if (!ranged) gfirst[nsrc] = chunks;
+    HIP_TRY(hipMemcpyAsync(d_lists + q.o_srcs, h + q.o_srcs, q.o_end - q.o_srcs, hipMemcpyHostToDevice, n->stream));
+    const int4* d_srcs = reinterpret_cast<const int4*>(d_lists + q.o_srcs);
+    const int* d_times = reinterpret_cast<const int*>(d_lists + q.o_times);
+    if (ranged)
+      HIP_TRY(launch_adj_gather_xcd(d_srcs, nsrc, d_times, n->d_row_ptr, n->d_adj_rb, n->d_tgt, n->d_dly, li_ring, st, R,
+                                    n0 + S - 1, grad, fp32, n->n_cu, n->stream));
+    else
+      HIP_TRY(launch_adj_gather(d_srcs, reinterpret_cast<const long long*>(d_lists + q.o_gfirst), nsrc, chunks, d_times,
+                                n->d_row_ptr, n->d_tgt, n->d_dly, li_ring, st, R, n0 + S - 1, grad, fp32, grid, n->stream));
   }
   HIP_TRY(hipEventRecord(n->ev1, n->stream));
   HIP_TRY(hipStreamSynchronize(n->stream));
@@ -2016,6 +2037,16 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
   for (int64_t i = 0; i < n->n_pad; ++i) sum += lp[i];
   *loss = sum / ((double)n->h.N * (double)S);
   return MC_OK;
+}
+
+int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) {
+  try {
+    return run_adjoint(n, a, grad, loss);
+  } catch (const std::bad_alloc&) {            // the work lists of the reverse pass
+    if (n->stream) (void)hipStreamSynchronize(n->stream);
+    n->failed = true;
+    return set_error(MC_ERR_OOM, "host allocation failed in the adjoint");
+  }
 }
 
 int mc_last_adjoint_ms(mc_net* n, double* forward_ms, double* reverse_ms) {

@@ -153,8 +153,7 @@ struct AdjSeg {
   const double* ck_y;      // checkpoint state at step a
   const double* ck_I;
   const int32_t* ck_r;
-  const long long* xseg;   // [len][ring_stride] integer input, with the drive if x_has_drive, else without
-  int x_has_drive;         // 1: xseg is the forward's full input record (no drive to redraw)
+  const long long* xseg;   // [len][ring_stride] integer input, drive included
   double* rec_y;           // [len][ring_stride] post-step y
   uint8_t* rec_t;          // [len][ring_stride] step type
   double* li_ring;         // [R][ring_stride] LI(m) at slot m & (R-1)
@@ -164,7 +163,7 @@ struct AdjSeg {
   unsigned long long* spike_count;   // recomputed spikes of this segment (added to)
 };
 constexpr int kGatherChunkHost = 256;     // must equal the gather kernel's chunk
-hipError_t launch_adj_seed(long long* xseg, const long long* ring_ckpt, long long stride, long long a, int rows,
+hipError_t launch_adj_seed(const DevNet& p, long long* xseg, const long long* ring_ckpt, long long a, int len, int rows,
                            hipStream_t s);
 hipError_t launch_adj_segment(const DevNet& p, const AdjSeg& a, hipStream_t s);
 hipError_t launch_adj_verify(const int2* spikes, int n, const uint8_t* rec_t, long long stride, long long a,
@@ -172,6 +171,14 @@ hipError_t launch_adj_verify(const int2* spikes, int n, const uint8_t* rec_t, lo
 hipError_t launch_adj_gather(const int4* srcs, const long long* first, int nsrc, long long n_items, const int* times,
                              const int64_t* row_ptr, const int32_t* tgt, const uint8_t* dly, const double* li_ring,
                              long long stride, int R, long long last_m, void* grad, bool fp32, int grid, hipStream_t s);
+
+// The same by target ranges, one per XCD: rb [n_pad][kAdjRanges+1] row bounds.
+constexpr int kAdjRanges = 8;
+bool adj_gather_ranged(long long stride);
+hipError_t launch_adj_bounds(const int64_t* row_ptr, const int32_t* tgt, long long n_pad, unsigned* rb, hipStream_t s);
+hipError_t launch_adj_gather_xcd(const int4* srcs, int nsrc, const int* times, const int64_t* row_ptr, const unsigned* rb,
+                                 const int32_t* tgt, const uint8_t* dly, const double* li_ring, long long stride, int R,
+                                 long long last_m, void* grad, bool fp32, int n_cu, hipStream_t s);
 
 // Persistent kernel with target-owner delivery into per-workgroup delay
 // buckets (mc_bucket.hip).  Workgroup g owns padded targets [bt0[g],
