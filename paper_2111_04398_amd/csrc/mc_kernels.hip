@@ -9,8 +9,8 @@
 //             count down; I <- P11 I + x; spike iff free and y >= theta,
 //             then y <- y_reset, r <- t_ref/h   (exact integration, FP64,
 //             no contraction);
-//   compact : spike flags -> dense ascending id list per workgroup with
-//             wavefront ballots and prefix sums, appended to the raster;
+//   compact : spike flags -> dense id list per workgroup, appended to the
+//             raster;
 //   deliver : every synapse s of every spiking row adds w_q[s] to
 //             ring[(n + d_s) mod 128][tgt_s] with an int64 atomic -- integer
 //             sums, so the result does not depend on the order.
@@ -24,7 +24,6 @@
 namespace mc {
 
 constexpr int kMaxBlock = 1024;
-constexpr int kMaxWaves = kMaxBlock / 64;
 constexpr int kMaxQuadsPerWg = 256;             // quads updated by one workgroup of k_step
 
 // ---------------------------------------------------------------------------
@@ -36,136 +35,138 @@ __device__ __forceinline__ void load_tables(const DevNet& p, uint64_t* s_table) 
   for (int k = threadIdx.x; k < p.n_pops * kTableLen; k += blockDim.x) s_table[k] = p.table[k];
 }
 
-// Exclusive prefix of per-lane counts c in [0, 7] across a wavefront from
-// three ballots over the bit planes of c.  Returns the lane's prefix; *total
-// receives the wave total.
-__device__ __forceinline__ int wave_prefix_small(int c, int* total) {
-  const unsigned lane = threadIdx.x & 63;
-  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const uint64_t b0 = __ballot(c & 1), b1 = __ballot(c & 2), b2 = __ballot(c & 4);
-  *total = __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
-  return __popcll(b0 & below) + 2 * __popcll(b1 & below) + 4 * __popcll(b2 & below);
+__device__ __forceinline__ uint64_t lane_swap(uint64_t v) {   // lanes 0<->1, 2<->3
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, 0xB1, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), 0xB1, 0xF, 0xF, true);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Upper 32 bits of word (lane & 3) of philox4x64_10(n, local, 0, kTagDrive;
+// seed, 0), for the four lanes of a quad together: even lanes hold the words
+// 0 and 1, odd lanes 2 and 3, and each multiplies once per round and swaps the
+// product with its neighbour -- half the 64-bit products of a lane that makes
+// the whole block, which lie on the step's critical path.
+__device__ __forceinline__ uint32_t quad_drive_word(uint64_t n, uint64_t local, uint64_t seed) {
+  const bool odd = threadIdx.x & 1;
+  const uint64_t mul = odd ? 0xCA5A826395121157ULL : 0xD2E7470EE14C6C93ULL;
+  const uint64_t weyl = odd ? 0xBB67AE8584CAA73BULL : 0x9E3779B97F4A7C15ULL;
+  uint64_t x = odd ? 0 : n, y = odd ? (uint64_t)kTagDrive : local, k = odd ? 0 : seed;
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    const uint64_t lo = mul * x, hi = __umul64hi(mul, x);
+    x = lane_swap(hi) ^ y ^ k;
+    y = lane_swap(lo);
+    k += weyl;
+  }
+  // lane 0: its x; 1: lane 0's y; 2: lane 3's x; 3: its y
+  const uint64_t send = odd ? x : y, got = lane_swap(send);
+  return hi32((threadIdx.x & 3) == 0 ? x : (threadIdx.x & 3) == 3 ? y : got);
 }
 
 // ---------------------------------------------------------------------------
 // One step: update + compaction + owner delivery.  Workgroup g updates the
-// quads [g*qpw, (g+1)*qpw) (one quad per thread), compacts its spikes into
-// an ascending list in LDS, appends them to its private raster segment and
-// walks their synapse rows with all of its threads.
+// quads [g*qpw, (g+1)*qpw), one neuron per thread and round, lists its spikes
+// in LDS, appends them to its private raster segment and walks their synapse
+// rows with all of its threads.
+//
+// A step of a small network is a chain of latencies, not work: step number,
+// state, drive, spikes, rows, atomics.  So every load that does not need the
+// step number or the spikes (state, row bounds, raster position) goes out
+// first, the bookkeeping is atomics nobody waits for, and a row of up to 8
+// entries per thread is one round of loads.
+// Per step, against one quad per lane of the first wavefronts with each load
+// where it is used: balanced network 10.4 -> 6.6 us, microcircuit at scale 0.3
+// 17.1 -> 11.8 us, full microcircuit 34 -> 29 us (there bound by the device
+// atomics of its rows).
 // ---------------------------------------------------------------------------
 template <bool kOwnerLists>
 __global__ __launch_bounds__(kMaxBlock) void k_step(DevNet p, int offset, int qpw, int wave_rows) {
+  constexpr int kRounds = 4;                    // neurons per thread at most (qpw <= threads)
+  constexpr int kAhead = 8;                     // entries of a row in flight per thread
   __shared__ uint64_t s_table[kMaxPops * kTableLen];
-  __shared__ int s_wcnt[kMaxWaves];
-  __shared__ int s_spk[4 * kMaxQuadsPerWg];
+  __shared__ int s_spk[4 * kMaxQuadsPerWg], s_len[4 * kMaxQuadsPerWg];
   __shared__ long long s_rs[4 * kMaxQuadsPerWg];
   __shared__ unsigned long long s_events;
+  __shared__ int s_total;
 
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const long long j0 = (long long)blockIdx.x * 4 * qpw;
+  const int nj = (int)min((long long)4 * qpw, 4 * p.n_quads - j0);
   const long long n = *p.step_base + offset;
-  load_tables(p, s_table);
-  __syncthreads();
-
-  const int tid = threadIdx.x;
-  const long long q = (long long)blockIdx.x * qpw + tid;
-  unsigned mask = 0;
-  if (tid < qpw && q < p.n_quads) {
-    const uint32_t pops = p.qpops[q];
-    const U64x4 v = philox4x64_10((uint64_t)n, (uint64_t)p.qlocal[q], 0, kTagDrive, p.qseed[q], 0);
-    long long* slot = p.ring + (size_t)(n & kRingMask) * p.ring_stride + 4 * q;
-    const longlong2 s01 = *reinterpret_cast<const longlong2*>(slot);
-    const longlong2 s23 = *reinterpret_cast<const longlong2*>(slot + 2);
-    *reinterpret_cast<longlong2*>(slot) = make_longlong2(0, 0);
-    *reinterpret_cast<longlong2*>(slot + 2) = make_longlong2(0, 0);
-    const long long sl[4] = {s01.x, s01.y, s23.x, s23.y};
-    double* yq = p.y + 4 * q;
-    double* Iq = p.I + 4 * q;
-    int* rq = p.r + 4 * q;
-    const double2 ya = *reinterpret_cast<const double2*>(yq), yb = *reinterpret_cast<const double2*>(yq + 2);
-    const double2 ia = *reinterpret_cast<const double2*>(Iq), ib = *reinterpret_cast<const double2*>(Iq + 2);
-    const int4 r4 = *reinterpret_cast<const int4*>(rq);
-    if (p.ck_y) {                        // adjoint forward: checkpoint before the update
-      const int k = (int)(n - p.ck_step0), every = (int)p.ck_every;   // windows hold at most 1e6 steps
-      if (k >= 0 && k % every == 0 && k / every < p.ck_count) {
-        const size_t at = (size_t)(k / every) * p.ring_stride + 4 * q;
-        *reinterpret_cast<double2*>(p.ck_y + at) = ya;
-        *reinterpret_cast<double2*>(p.ck_y + at + 2) = yb;
-        *reinterpret_cast<double2*>(p.ck_I + at) = ia;
-        *reinterpret_cast<double2*>(p.ck_I + at + 2) = ib;
-        *reinterpret_cast<int4*>(p.ck_r + at) = r4;
-      }
-    }
-    double y[4] = {ya.x, ya.y, yb.x, yb.y};
-    double I[4] = {ia.x, ia.y, ib.x, ib.y};
-    int r[4] = {r4.x, r4.y, r4.z, r4.w};
-    uint8_t type[4];
-    long long xin[4] = {sl[0], sl[1], sl[2], sl[3]};
+  const long long rbase = p.raster_cnt[blockIdx.x];
+  double y[kRounds], I[kRounds];
+  int r[kRounds];
+  uint32_t pops[kRounds];
+  uint64_t local[kRounds], seed[kRounds];
+  long long rs[kRounds], re[kRounds];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const unsigned pop = (pops >> (8 * k)) & 0xFFu;
-      if (pop == 0xFFu) continue;  // padding neuron: never updated, never spikes
-      const int cnt = poisson_from_u32(s_table + pop * kTableLen, hi32(pick(v, k)));
-      xin[k] = sl[k] + (long long)cnt * p.jext_q;
-      if (lif_step(p, y[k], I[k], r[k], xin[k], type[k])) mask |= 1u << k;
+  for (int c = 0; c < kRounds; ++c) {
+    const int jl = tid + c * nthr;
+    if (c * nthr < nj && jl < nj) {
+      const long long j = j0 + jl, q = j >> 2;
+      pops[c] = p.qpops[q]; local[c] = (uint64_t)p.qlocal[q]; seed[c] = p.qseed[q];
+      y[c] = p.y[j]; I[c] = p.I[j]; r[c] = p.r[j];
+      rs[c] = p.row_ptr[j]; re[c] = p.row_ptr[j + 1];
     }
-    if (p.xrec && n - p.xrec_step0 >= 0 && n - p.xrec_step0 < p.xrec_steps) {
-      long long* xr = p.xrec + (size_t)(n - p.xrec_step0) * p.ring_stride + 4 * q;
-      *reinterpret_cast<longlong2*>(xr) = make_longlong2(xin[0], xin[1]);
-      *reinterpret_cast<longlong2*>(xr + 2) = make_longlong2(xin[2], xin[3]);
-    }
-    *reinterpret_cast<double2*>(yq) = make_double2(y[0], y[1]);
-    *reinterpret_cast<double2*>(yq + 2) = make_double2(y[2], y[3]);
-    *reinterpret_cast<double2*>(Iq) = make_double2(I[0], I[1]);
-    *reinterpret_cast<double2*>(Iq + 2) = make_double2(I[2], I[3]);
-    *reinterpret_cast<int4*>(rq) = make_int4(r[0], r[1], r[2], r[3]);
   }
+  load_tables(p, s_table);
+  if (tid == 0) { s_events = 0; s_total = 0; }
+  __syncthreads();
 
-  // compaction: ascending ids (thread order = quad order, bit order = id order)
-  int wtotal;
-  const int c = __popc(mask);
-  const int pre = wave_prefix_small(c, &wtotal);
-  const int wave = tid >> 6;
-  if ((tid & 63) == 0) s_wcnt[wave] = wtotal;
-  if (tid == 0) s_events = 0;
-  __syncthreads();
-  int woff = 0, total = 0;
-  const int nw = blockDim.x >> 6;
-  for (int w = 0; w < nw; ++w) { const int t = s_wcnt[w]; woff += (w < wave) ? t : 0; total += t; }
-  if (mask) {
-    int pos = woff + pre;
-    for (int k = 0; k < 4; ++k)
-      if (mask & (1u << k)) s_spk[pos++] = (int)(4 * q + k);
+  long long ck = -1;                            // adjoint forward: the checkpoint to write before the update
+  if (p.ck_y && n >= p.ck_step0) {
+    const unsigned k = (unsigned)(n - p.ck_step0), every = (unsigned)p.ck_every;   // windows hold at most 1e6 steps
+    if (k % every == 0 && k / every < p.ck_count) ck = k / every;
+  }
+  const bool xr = p.xrec && n >= p.xrec_step0 && n - p.xrec_step0 < p.xrec_steps;
+#pragma unroll
+  for (int c = 0; c < kRounds; ++c) {
+    const int jl = tid + c * nthr;
+    if (c * nthr < nj && jl < nj) {
+      const long long j = j0 + jl;
+      long long* slot = p.ring + (size_t)(n & kRingMask) * p.ring_stride + j;
+      long long xin = *slot;
+      *slot = 0;
+      if (ck >= 0) {
+        const size_t at = (size_t)ck * p.ring_stride + j;
+        p.ck_y[at] = y[c]; p.ck_I[at] = I[c]; p.ck_r[at] = r[c];
+      }
+      const uint32_t u = quad_drive_word((uint64_t)n, local[c], seed[c]);
+      const unsigned pop = (pops[c] >> (8 * (tid & 3))) & 0xFFu;
+      if (pop != 0xFFu) {                       // (padding neurons are never updated, never spike)
+        xin += (long long)poisson_from_u32(s_table + pop * kTableLen, u) * p.jext_q;
+        uint8_t type;
+        if (lif_step(p, y[c], I[c], r[c], xin, type)) {
+          const int pos = atomicAdd(&s_total, 1);   // in any order: the sums are of integers, the read-back sorts a step
+          s_spk[pos] = (int)j;
+          s_rs[pos] = rs[c];
+          s_len[pos] = (int)(re[c] - rs[c]);
+          atomicAdd(&s_events, (unsigned long long)(re[c] - rs[c]));
+          atomicAdd(p.wg_spikes + (size_t)blockIdx.x * p.n_pops + pop, 1ull);
+        }
+        p.y[j] = y[c]; p.I[j] = I[c]; p.r[j] = r[c];
+      }
+      if (xr) p.xrec[(size_t)(n - p.xrec_step0) * p.ring_stride + j] = xin;
+    }
   }
   __syncthreads();
+  const int total = s_total;
   if (total == 0) return;
 
-  // row bounds, raster append, counters
-  for (int s = tid; s < total; s += blockDim.x) {
-    const int i = s_spk[s];
-    const long long rs = p.row_ptr[i], re = p.row_ptr[i + 1];
-    s_rs[s] = rs;
-    atomicAdd(&s_events, (unsigned long long)(re - rs));
-  }
-  const long long rbase = p.raster_cnt[blockIdx.x];
   const bool fits = rbase + total <= p.raster_cap;
-  for (int s = tid; s < total && fits; s += blockDim.x)
+  for (int s = tid; s < total && fits; s += nthr)
     p.raster[(size_t)blockIdx.x * p.raster_cap + rbase + s] = make_int2((int)n, s_spk[s]);
-  __syncthreads();
   if (tid == 0) {
     if (fits) p.raster_cnt[blockIdx.x] = rbase + total;
     else atomicOr(p.overflow, 1u);
-    p.wg_events[blockIdx.x] += s_events;
-    for (int s = 0; s < total; ++s) {
-      const int i = s_spk[s];
-      const unsigned pop = (p.qpops[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-      p.wg_spikes[(size_t)blockIdx.x * p.n_pops + pop] += 1ull;
-    }
+    atomicAdd(p.wg_events + blockIdx.x, s_events);
   }
 
   if (kOwnerLists) {
     // target-owner scheme: the spikes go to their instance's list of this
     // step; the owner kernel delivers them
     const int par = (int)(n & 1);
-    for (int s = tid; s < total; s += blockDim.x) {
+    for (int s = tid; s < total; s += nthr) {
       const int i = s_spk[s];
       const int b = p.qinst[i >> 2];
       const int pos = atomicAdd(&p.icnt[par * p.n_inst + b], 1);
@@ -176,26 +177,22 @@ __global__ __launch_bounds__(kMaxBlock) void k_step(DevNet p, int offset, int qp
 
   // owner delivery: all threads walk each spiking row in turn, or (wave_rows)
   // every wavefront walks whole rows, the spikes dealt round robin
-  const long long nn = n;
-  const int rstep = wave_rows ? (int)(blockDim.x >> 6) : 1;
-  for (int s = wave_rows ? (tid >> 6) : 0; s < total; s += rstep) {
-    const long long rs = s_rs[s];
-    const long long re = p.row_ptr[s_spk[s] + 1];
-    long long e = rs + (wave_rows ? (tid & 63) : tid);
-    const int stride = wave_rows ? 64 : blockDim.x;
-    for (; e + 3 * stride < re; e += 4 * stride) {
-      int t[4], w[4], d[4];
+  const int step = wave_rows ? nthr >> 6 : 1, stride = wave_rows ? 64 : nthr;
+  for (int s = wave_rows ? tid >> 6 : 0; s < total; s += step) {
+    const long long row = s_rs[s];
+    const int len = s_len[s];
+    for (int e = wave_rows ? tid & 63 : tid; e < len; e += kAhead * stride) {
+      int t[kAhead], w[kAhead], d[kAhead];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { t[u] = p.tgt[e + u * stride]; w[u] = p.wq[e + u * stride]; d[u] = p.dly[e + u * stride]; }
+      for (int k = 0; k < kAhead; ++k) {
+        const int at = e + k * stride;
+        if (at < len) { t[k] = p.tgt[row + at]; w[k] = p.wq[row + at]; d[k] = p.dly[row + at]; }
+      }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        atomicAdd(reinterpret_cast<unsigned long long*>(p.ring + (size_t)((nn + d[u]) & kRingMask) * p.ring_stride + t[u]),
-                  (unsigned long long)(long long)w[u]);
-    }
-    for (; e < re; e += stride) {
-      const int t = p.tgt[e], w = p.wq[e], d = p.dly[e];
-      atomicAdd(reinterpret_cast<unsigned long long*>(p.ring + (size_t)((nn + d) & kRingMask) * p.ring_stride + t),
-                (unsigned long long)(long long)w);
+      for (int k = 0; k < kAhead; ++k)
+        if (e + k * stride < len)
+          atomicAdd(reinterpret_cast<unsigned long long*>(p.ring + (size_t)((n + d[k]) & kRingMask) * p.ring_stride + t[k]),
+                    (unsigned long long)(long long)w[k]);
     }
   }
 }
