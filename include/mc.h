@@ -142,10 +142,12 @@ enum { MC_SCHEME_STEP_KERNELS = 0,   /* one kernel per step (update, then source
 typedef struct mc_launch {
   uint32_t struct_size;
   int32_t scheme;
-  int32_t block;                 /* threads per workgroup: 64..1024, multiple of 64 */
+  int32_t block;                 /* threads per workgroup: 64..1024, multiple of 64 (persistent: where every
+                                    workgroup has a compute unit to itself, further wavefronts, up to 768
+                                    threads, only deliver) */
   int32_t neurons_per_wg;        /* neurons updated by one workgroup: multiple of 4, <= 4*block, <= 1024
                                     (persistent: <= block; target owner: the targets of one delivery block,
-                                    its update kernel takes one quad per thread; buckets: <= min(4092,
+                                    its update kernel takes 4*block neurons, at most 1024; buckets: <= min(4092,
                                     64*block)); 0: automatic */
   int32_t steps_per_graph;       /* steps captured per graph replay / per persistent launch (>= 1) */
   int32_t rows_per_wave;         /* step kernels' delivery: 0 = all threads of a workgroup walk each
@@ -203,7 +205,7 @@ int mc_simulate(mc_net* net, int64_t steps);
  * hipMalloc or hipFree, no graph instantiation, no raster drain.  The
  * kernels' spike records (the scratch mc_simulate keeps in
  * library-allocated memory) come from a file-scope device array of about
- * 0.25 MiB (room for 512 workgroups of 512 targets) that each GPU holds until
+ * 0.31 MiB (room for 512 workgroups of 512 targets) that each GPU holds until
  * the process ends.  The records are cleared by a kernel at the start of
  * every call.  Every call on one GPU shares that GPU's array, so calls that
  * overlap on one GPU (two networks on concurrent streams) race: serialize

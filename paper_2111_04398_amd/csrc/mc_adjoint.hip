@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_adj_bounds(const int64_t* row_ptr
 // -- is about its 4 MB of L2.  In the plain gather each 8-byte value comes as a
 // line of its own from the memory side.  A wavefront takes whole sub-rows, and
 // the launch has 3/4 of the wavefronts a CU holds: more widen the span of
-// steps.  Full microcircuit, 100-step segments: 439 -> 330 us on average.
+// steps.  Full microcircuit, 100-step segments: 439 -> 340-370 us on average.
 // Launches of a few steps each, to bound the span harder, left too few
 // sub-rows per launch: 690 us per segment.
 template <typename G>

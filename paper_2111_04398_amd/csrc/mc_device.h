@@ -98,13 +98,12 @@ constexpr int kRecSlots = 4;            // spike records (and side arrays) per w
 __host__ __device__ inline size_t persist_record_words(int G) { return (size_t)G * kRecSlots * kPersistFlagStride; }
 __host__ __device__ inline size_t persist_flag_words(int G) { return persist_record_words(G) + kPersistFlagStride; }
 // Spike records of the LDS-window scheme: word 0 of every workgroup's record
-// of a step side by side (a poll of 64 of them reads four lines), then the
-// bitmap words (a line per record).
+// of a step, four to a 128-byte line, then the bitmap words (a line per
+// record).  The empty exchange loop of 254 workgroups takes, with word 0 every
+// 8 / 16 / 32 / 64 / 128 / 256 bytes, 2.44 / 2.10 / 1.88 / 1.93 / 2.23 / 2.22
+// us per step: fewer lines per poll against fewer stores to one line.
 constexpr int kWinMapWords = 16;
-#ifndef W0STRIDE
-#define W0STRIDE 4
-#endif
-constexpr int kWord0Stride = W0STRIDE;
+constexpr int kWord0Stride = 4;
 __host__ __device__ inline size_t window_word0(int G, int slot, int g) { return ((size_t)slot * ((G + 15) / 16 * 16) + g) * kWord0Stride; }
 __host__ __device__ inline size_t window_map(int G, int slot, int g) {
   return window_word0(G, kRecSlots, 0) + ((size_t)slot * G + g) * kWinMapWords;

@@ -15,7 +15,8 @@
 // Packed rows.  Delivery reads a copy of the store made for this launch shape:
 // every row keeps its place (row_ptr) but is reordered by target workgroup,
 // the workgroups in XCD order, one 8-byte word per synapse (weight, and the
-// delay and local target as one offset into the LDS window), with the sub-row bounds of every (row, workgroup) in `off`.
+// delay and local target as one offset into the LDS window), with the sub-row
+// bounds of every (row, workgroup) in `off`.
 // One load per synapse instead of three, and the 32 workgroups of an XCD read
 // adjacent parts of a row, so that cache lines are shared inside one L2.
 //
@@ -62,6 +63,12 @@
 // the step needs no L2 writeback or invalidate.  Every wait is bounded in
 // time (wall clock); on timeout the kernel sets error bit 2 and every
 // wavefront leaves its loop.
+//
+// Bound: latency.  The empty loop of the same exchange takes 1.88 us per step
+// (254 workgroups); a quiet step of the full microcircuit 2.6-3.2 us, a burst
+// about 19 ns per spike.  Mean over 10,000 steps (barriers, three arrays per
+// synapse and a side array of ids -> this form): full microcircuit 9.0 -> 4.0
+// us, balanced network 5.0 -> 2.6 us, calls of 20 steps 143-160 -> 86-92 us.
 #pragma clang fp contract(off)
 
 #include <algorithm>
