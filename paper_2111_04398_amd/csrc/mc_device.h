@@ -94,7 +94,7 @@ struct PersistArgs {
   int list_cap;
 };
 constexpr int kPersistFlagStride = 8;
-constexpr int kRecSlots = 4;            // spike records (and side arrays) per workgroup, by step mod 4
+constexpr int kRecSlots = 4;            // spike records per workgroup, by step mod 4
 __host__ __device__ inline size_t persist_record_words(int G) { return (size_t)G * kRecSlots * kPersistFlagStride; }
 __host__ __device__ inline size_t persist_flag_words(int G) { return persist_record_words(G) + kPersistFlagStride; }
 // Spike records of the LDS-window scheme: word 0 of every workgroup's record
