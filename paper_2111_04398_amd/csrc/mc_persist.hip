@@ -73,6 +73,7 @@
 
 #include <algorithm>
 #include "mc_device.h"
+#include "mc_queue.h"
 
 namespace mc {
 
@@ -149,6 +150,25 @@ __device__ __forceinline__ int wave_incl(int x) {
 // A value that is the same in every lane, into a scalar register.
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ unsigned uni(unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); }
+// A wavefront's view of the id queue (see claim_ids): lane k reads the id k
+// places on.  The LDS operations of a wavefront are performed in the order in
+// which it issues them; the fence keeps the compiler to it and costs nothing.
+struct IdQueue {
+  const unsigned* slots;
+  unsigned* s_head;
+  int lane;
+  unsigned id;
+  __device__ __forceinline__ unsigned head() { return uni(lds_rlx(s_head)); }
+  __device__ __forceinline__ void read(unsigned h) {
+    id = lds_rlx(&slots[(h + (unsigned)lane) & (kQueue - 1)]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  __device__ __forceinline__ unsigned take(unsigned h, unsigned to) {
+    if (lane == 0)
+      __hip_atomic_compare_exchange_strong(s_head, &h, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return uni(h);
+  }
+};
 // Kernel arguments are loaded as tuples of 16 scalar registers, which spill
 // and return as a whole; what the step loop uses is copied out one by one,
 // the constants of the update into vector registers.
@@ -484,11 +504,10 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
         __hip_atomic_fetch_add(&s_done[st], (unsigned)__popcll(same), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   };
-  // All events of ids [h, h + c) of the queue, c <= per: a group of 1 << ls
-  // lanes per id, kFew entries in flight per lane.  The fewest instructions
-  // for the few spikes of a quiet step.
-  auto deliver_few = [&](unsigned h, unsigned c) {
-    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];     // (lanes >= c unused)
+  // All events of the c claimed ids (lane k holds id k in qq; lanes >= c
+  // unused), c <= per: a group of 1 << ls lanes per id, kFew entries in flight
+  // per lane.  The fewest instructions for the few spikes of a quiet step.
+  auto deliver_few = [&](unsigned qq, unsigned c) {
     const unsigned q = (unsigned)__shfl((int)qq, sub, 64);
     const bool mine = sub < (int)c;
     const unsigned id = mine ? q & 0x3FFFFu : 0u;
@@ -522,14 +541,13 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
     }
     delivered(qq, c, far);
   };
-  // All events of ids [h, h + c), c <= 64: a lane per id finds its sub-row and
+  // All events of the c claimed ids, c <= 64: a lane per id finds its sub-row and
   // cuts it into units of 1 << ls entries, listed in LDS; then the wavefront
   // walks the units, 64 / L at a time (a slot), two groups of kSlots slots in
   // flight.  One chain of dependent loads per claim and few idle lanes: the
   // full microcircuit's bursts (600 to 3,000 spikes a step) went from 35 to 22 ns
   // per spike with the units and to 19 with 12 wavefronts instead of 8.
-  auto deliver_many = [&](unsigned h, unsigned c) {
-    const unsigned qq = s_q[(h + lane) & (kQueue - 1)];
+  auto deliver_many = [&](unsigned qq, unsigned c) {
     const bool mine = lane < (int)c;
     const unsigned id = mine ? qq & 0x3FFFFu : 0u;
     const unsigned* o = off + (size_t)id * (unsigned)(G + 1);
@@ -667,7 +685,7 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
         todo &= ~few;                           // nothing but empty records
       } else {
         const int x = wave_incl((int)cf);
-        const bool ok = x <= (int)(qcap - (tail - gone));   // room in the queue: the accepted lanes are a prefix
+        const bool ok = x <= (int)queue_room(qcap, tail, gone);   // room in the queue: the accepted lanes are a prefix
         if (ok) {
           todo &= ~few;
           unsigned o = tail + (unsigned)x - cf;
@@ -720,7 +738,7 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
               const bool good = own[q] >= 0 && ((bad >> (lane & 48)) & 0xFFFFull) == 0;
               unsigned long long mm = (good && need[q]) ? wk[q] & ((1ull << kMapBits) - 1) : 0ull;
               const int x = wave_incl(__popcll(mm)), xr = __shfl(x, lane | 15, 64);   // up to the end of the record
-              const bool ok = good && xr <= (int)(qcap - (tail - gone));
+              const bool ok = good && xr <= (int)queue_room(qcap, tail, gone);
               if (ok) {
                 unsigned o = tail + (unsigned)(x - __popcll(mm));
                 const unsigned b = ((unsigned)((own[q] + 64 * k) * B) | qtag) + (unsigned)(kMapBits * L);
@@ -756,33 +774,16 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
     }
     // ---- deliver: claim ids and add all their events ---------------------------
     if (delivers || (pit == steps && uit >= (isU ? steps : 0))) {
-      unsigned h = 0, c = 0;
-      {
-        unsigned t = uni(lds_acq(&s_tail));
-        // later steps' ids are not what an update waits for: it leaves them to
-        // the other wavefronts unless many pile up (a burst)
-        if (limited && (int)(t - limit) <= nw * per) t = limit;
-        h = uni(lds_rlx(&s_head));    // (may be past t by now)
-        if ((int)(t - h) > 0) {
-          if (lane == 0) {
-            while ((int)(t - h) > 0) {
-              // (a short queue is shared out in single rounds, a long one evenly)
-              const unsigned want = min(t - h, (unsigned)min(64, max(per, (int)(t - h) / nw)));
-              if (__hip_atomic_compare_exchange_strong(&s_head, &h, h + want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                c = want;
-                break;
-              }
-            }
-          }
-          h = uni(h);
-          c = uni(c);
-        }
-      }
+      unsigned t = uni(lds_acq(&s_tail));
+      // later steps' ids are not what an update waits for: it leaves them to
+      // the other wavefronts unless many pile up (a burst)
+      if (limited && (int)(t - limit) <= nw * per) t = limit;
+      IdQueue queue{s_q, &s_head, lane, 0u};
+      const unsigned c = claim_ids(queue, t, (unsigned)per, (unsigned)nw);
       if (c > 0) {
         const long long tq = kTime ? wall_clock64() : 0;
-        if (c <= (unsigned)per) deliver_few(h, c);
-        else deliver_many(h, c);
+        if (c <= (unsigned)per) deliver_few(queue.id, c);
+        else deliver_many(queue.id, c);
         if (kTime) { const long long t = wall_clock64(); ph[4] += t - tq; tp_idle += t - tq; }
         t_wait = 0;
         continue;
