@@ -209,7 +209,10 @@ int mc_simulate(mc_net* net, int64_t steps);
  * the process ends.  The records are cleared by a kernel at the start of
  * every call.  Every call on one GPU shares that GPU's array, so calls that
  * overlap on one GPU (two networks on concurrent streams) race: serialize
- * them.  Same trajectory, raster and counters as mc_simulate(steps).
+ * them.  Same trajectory, raster and counters as mc_simulate(steps).  A
+ * captured call counts its steps once, at capture; a graph that is replayed
+ * more often runs further steps, whose spikes mc_get_spikes returns like any
+ * other (at most the steps of mc_reserve between two read-backs).
  * Errors: STATE (another scheme, or a host-only/failed handle), RANGE (a
  * persistent shape beyond the scratch, step count beyond int32),
  * BUFFER_TOO_SMALL (more steps than the raster holds without a drain: call

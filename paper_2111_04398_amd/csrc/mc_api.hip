@@ -193,6 +193,7 @@ struct mc_net {
   unsigned* d_wbad = nullptr;          // weight update check flag
   int64_t cap_steps = 0;               // steps the raster segments can absorb between drains
   int64_t steps_since_drain = 0;
+  bool captured = false;               // launches of this network went into a caller's graph, whose replays nobody counts
   // drained raster (dense ids), sorted by (step, id); a deque, so that growing
   // it never copies the spikes already held (long runs hold tens of millions)
   std::deque<int32_t> r_step, r_id;
@@ -217,7 +218,7 @@ struct mc_net {
   int64_t* d_inst_off = nullptr;       // [n_inst+1] dense
   int* d_rwork = nullptr;              // scratch of a long read-back
   int64_t rwork_cap = 0;
-  long long* h_spk = nullptr;          // pinned: 3 header words, steps, ids
+  long long* h_spk = nullptr;          // pinned: kRasterHead header words, steps, ids
   int64_t spk_cap = 0;                 // spikes it holds
   unsigned* d_adj_rb = nullptr;        // the adjoint's target ranges [n_pad][kAdjRanges+1], made at its first use
   void* h_stage = nullptr;             // pinned staging of the adjoint's work lists
@@ -340,7 +341,7 @@ int64_t spike_bound(int64_t neurons, int64_t steps, int ref) {
 int reserve_spikes(mc_net* n, int64_t spikes) {
   if (n->h_spk && n->spk_cap >= spikes) return MC_OK;
   if (n->h_spk) { (void)hipHostFree(n->h_spk); n->h_spk = nullptr; n->spk_cap = 0; }
-  HIP_TRY(hipHostMalloc((void**)&n->h_spk, sizeof(long long) * 4 + sizeof(int) * 2 * (size_t)spikes, hipHostMallocDefault));
+  HIP_TRY(hipHostMalloc((void**)&n->h_spk, sizeof(long long) * kRasterHead + sizeof(int) * 2 * (size_t)spikes, hipHostMallocDefault));
   n->spk_cap = spikes;
   return MC_OK;
 }
@@ -353,7 +354,7 @@ int reserve_spikes(mc_net* n, int64_t spikes) {
 int drain(mc_net* n, hipEvent_t upto = nullptr) {
   if (!n->d_raster) return MC_OK;
   hipStream_t s = upto ? n->aux : n->stream;
-  if (n->steps_since_drain == 0) {             // nothing simulated since the last one
+  if (n->steps_since_drain == 0 && !n->captured) {   // nothing simulated since the last one
     if (!upto) HIP_TRY(hipStreamSynchronize(s));
     return MC_OK;
   }
@@ -363,12 +364,10 @@ int drain(mc_net* n, hipEvent_t upto = nullptr) {
   RasterArgs a{};
   auto outputs = [&] {
     a.head = n->h_spk;
-    a.out_step = reinterpret_cast<int*>(n->h_spk + 4);
+    a.out_step = reinterpret_cast<int*>(n->h_spk + kRasterHead);
     a.out_id = a.out_step + n->spk_cap;
   };
   a.raster = n->d_raster; a.cap = n->raster_cap; a.cnt = n->d_raster_cnt; a.n_seg = n->n_wg;
-  a.lo = (int)(n->step - n->steps_since_drain);
-  a.span = (int)n->steps_since_drain;
   a.overflow = n->d_overflow; a.inst_pad = n->d_inst_base; a.inst_off = n->d_inst_off; a.n_inst = n->h.n_inst;
   outputs();
   HIP_TRY(launch_raster_small(a, s));
@@ -384,9 +383,11 @@ int drain(mc_net* n, hipEvent_t upto = nullptr) {
     n->failed = true;
     return set_error(MC_ERR_STATE, "raster segment overflow (internal capacity error)");
   }
-  if (n->h_spk[2] == 0) {                      // more than one workgroup reads back
+  if (n->h_spk[2] == 0 && total > 0) {         // more than one workgroup reads back
     if (total > 2147483647LL) return set_error(MC_ERR_RANGE, "more than 2^31 spikes between two read-backs");
-    const int64_t span = n->steps_since_drain;
+    const int64_t span = n->h_spk[4] - n->h_spk[3] + 1;
+    a.lo = (int)n->h_spk[3];
+    a.span = (int)span;
     // (room to spare: the spikes of equal spans vary with the activity)
     if (total > n->spk_cap && (rc = reserve_spikes(n, total + total / 2)) != MC_OK) return rc;
     outputs();
@@ -400,6 +401,10 @@ int drain(mc_net* n, hipEvent_t upto = nullptr) {
     int *hist = n->d_rwork, *off = hist + span + 64, *cursor = off + span + 64, *bucket = cursor + span + 64;
     HIP_TRY(launch_raster_order(a, n->n_pad, hist, off, cursor, bucket, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (n->h_spk[5] != total) {
+      n->failed = true;
+      return set_error(MC_ERR_STATE, "read-back of the raster lost spikes (internal error)");
+    }
   }
   try {
     n->r_step.insert(n->r_step.end(), a.out_step, a.out_step + total);
@@ -789,6 +794,13 @@ int build_graph(mc_net* n) {
   return MC_OK;
 }
 
+// Notes that a call's launches go into a graph that the caller captures.
+void note_capture(mc_net* n) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(n->stream, &st) != hipSuccess) (void)hipGetLastError();
+  else if (st != hipStreamCaptureStatusNone) n->captured = true;
+}
+
 constexpr int kLaunchEvents = 128;
 
 // Records the event that opens (begin) or closes a timed persistent launch on
@@ -1074,6 +1086,7 @@ int mc_simulate(mc_net* n, int64_t steps) {
   if (!device_ready(n)) return set_error(MC_ERR_STATE, "handle is host-only, failed or NULL");
   if (steps < 0) return set_error(MC_ERR_INVALID_ARG, "steps < 0");
   if (n->step + steps > 2147483647LL) return set_error(MC_ERR_RANGE, "step count beyond int32 raster steps");
+  note_capture(n);
   HIP_TRY(hipEventRecord(n->ev0, n->stream));
   n->launches_timed = 0;
   n->steps_timed = 0;
@@ -1101,6 +1114,7 @@ int mc_simulate_noalloc(mc_net* n, int64_t steps) {
   if (cur != n->device) return set_error(MC_ERR_INVALID_ARG, "the network's device is not the current device");
   unsigned long long* rec = nullptr;
   HIP_TRY(noalloc_scratch(n->device, &rec));
+  note_capture(n);
   HIP_TRY(hipEventRecord(n->ev0, n->stream));
   n->launches_timed = 0;
   n->steps_timed = 0;

@@ -256,15 +256,16 @@ struct RasterArgs {
   long long cap;
   long long* cnt;              // [n_seg] entries of every segment; emptied once they have been read
   int n_seg;
-  int lo, span;                // the segments hold steps lo .. lo + span - 1
+  int lo, span;                // the long way: the segments hold steps lo .. lo + span - 1 (from head)
   const unsigned* overflow;    // error bits of the simulation kernels
   const int64_t* inst_pad;     // [n_inst+1] first padded id of every instance
   const int64_t* inst_off;     // [n_inst+1] first dense id
   int n_inst;
   int* out_step;               // pinned host memory
   int* out_id;
-  long long* head;             // pinned, 3 words (see k_raster_small)
+  long long* head;             // pinned, kRasterHead words (see k_raster_small and k_raster_scan)
 };
+constexpr int kRasterHead = 8;
 constexpr int kRasterSmall = 2048;        // spikes read back by one workgroup
 hipError_t launch_raster_small(const RasterArgs& a, hipStream_t s);
 // Any number of spikes: hist [span], off [span+1],

@@ -17,6 +17,8 @@
 // workgroup per step: by rank for a few, else through a bitmap over the ids (a
 // neuron spikes at most once per step), whose cost does not depend on the
 // number of spikes.
+#include <algorithm>
+
 #include "mc_device.h"
 
 namespace mc {
@@ -59,7 +61,10 @@ __device__ __forceinline__ int scan_block(int v, int* s_tmp, int* total) {
 }  // namespace
 
 // head[0] = spikes, head[1] = error bits, head[2] = 1 if they have been
-// written (else there are too many: the caller takes the long way).
+// written; else there are too many, the caller takes the long way, and head[3]
+// and head[4] are their first and last step.  The range comes from the spikes:
+// a graph that the program captured may have run any number of steps since the
+// last read-back.
 __global__ __launch_bounds__(kSmallBlock) void k_raster_small(RasterArgs a) {
   __shared__ int s_pre[kMaxSeg + 1];
   __shared__ unsigned long long s_key[kSmall];
@@ -76,11 +81,21 @@ __global__ __launch_bounds__(kSmallBlock) void k_raster_small(RasterArgs a) {
   if (!small) {
     // the long way needs the exact total
     unsigned long long* sum = reinterpret_cast<unsigned long long*>(s_key);
-    if (tid == 0) sum[0] = 0;
+    int* range = reinterpret_cast<int*>(s_key + 1);
+    if (tid == 0) { sum[0] = 0; range[0] = 0x7FFFFFFF; range[1] = -1; }
     __syncthreads();
     if (mine) atomicAdd(sum, (unsigned long long)mine);
+    for (int k = tid * per; k < min((tid + 1) * per, a.n_seg); ++k) {
+      const long long c = a.cnt[k];        // (a segment is ordered by step)
+      if (c == 0) continue;
+      atomicMin(&range[0], a.raster[(size_t)k * a.cap].x);
+      atomicMax(&range[1], a.raster[(size_t)k * a.cap + c - 1].x);
+    }
     __syncthreads();
-    if (tid == 0) { a.head[0] = (long long)sum[0]; a.head[1] = *a.overflow; a.head[2] = 0; }
+    if (tid == 0) {
+      a.head[0] = (long long)sum[0]; a.head[1] = *a.overflow; a.head[2] = 0;
+      a.head[3] = range[0]; a.head[4] = range[1];
+    }
     return;
   }
   for (int k = tid * per; k < min((tid + 1) * per, a.n_seg); ++k) {
@@ -129,11 +144,12 @@ __global__ void k_raster_hist(RasterArgs a, int* hist) {
   }
 }
 
-// off[k] = spikes before step lo + k (k <= span); cursor[k] likewise (k < span).
-__global__ __launch_bounds__(kSmallBlock) void k_raster_scan(const int* hist, int span, int* off, int* cursor) {
+// off[k] = spikes before step lo + k (k <= span); cursor[k] likewise (k < span);
+// head[5] = spikes in all.
+__global__ __launch_bounds__(kSmallBlock) void k_raster_scan(const int* hist, int span, int* off, int* cursor, long long* head) {
   __shared__ int s_tmp[kSmallBlock / 64];
-  const int per = (span + kSmallBlock - 1) / kSmallBlock;
-  const int b = min((int)threadIdx.x * per, span), e = min(b + per, span);
+  const int per = (int)(((long long)span + kSmallBlock - 1) / kSmallBlock);
+  const int b = (int)min((long long)threadIdx.x * per, (long long)span), e = (int)min((long long)b + per, (long long)span);
   int mine = 0;
   for (int k = b; k < e; ++k) mine += hist[k];
   int total;
@@ -144,7 +160,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_raster_scan(const int* hist, in
     cursor[k] = at;
     at += h;
   }
-  if (threadIdx.x == 0) off[span] = total;
+  if (threadIdx.x == 0) { off[span] = total; head[5] = total; }
 }
 
 // Every spike's padded id into its step's bucket (any order).
@@ -158,15 +174,16 @@ __global__ void k_raster_scatter(RasterArgs a, int* cursor, int* bucket) {
   }
 }
 
-// Step lo + blockIdx.x: its ids in ascending order, dense, to out_id; the
-// steps to out_step; the first workgroup empties the segments.
-__global__ __launch_bounds__(kStepBlock) void k_raster_sort(RasterArgs a, const int* off, const int* bucket, long long n_pad) {
+// Step lo + at, at = first + blockIdx.x: its ids in ascending order, dense, to
+// out_id; the steps to out_step; the first workgroup empties the segments.
+__global__ __launch_bounds__(kStepBlock) void k_raster_sort(RasterArgs a, int first, const int* off, const int* bucket,
+                                                            long long n_pad) {
   __shared__ unsigned s_map[kMapIds / 32];
   __shared__ int s_tmp[kStepBlock / 64];
-  const int tid = threadIdx.x, b = off[blockIdx.x], c = off[blockIdx.x + 1] - b;
-  if (blockIdx.x == 0)
+  const int tid = threadIdx.x, at = first + (int)blockIdx.x, b = off[at], c = off[at + 1] - b;
+  if (at == 0)
     for (int k = tid; k < a.n_seg; k += kStepBlock) a.cnt[k] = 0;
-  for (int k = tid; k < c; k += kStepBlock) a.out_step[b + k] = a.lo + (int)blockIdx.x;
+  for (int k = tid; k < c; k += kStepBlock) a.out_step[b + k] = a.lo + at;
   if (c <= kRank) {
     int* s_id = reinterpret_cast<int*>(s_map);
     const int id = (tid < c) ? bucket[b + tid] : 0;
@@ -178,13 +195,13 @@ __global__ __launch_bounds__(kStepBlock) void k_raster_sort(RasterArgs a, const 
     return;
   }
   int done = 0;
-  for (long long first = 0; first < n_pad; first += kMapIds) {
-    const int words = (int)((min((long long)kMapIds, n_pad - first) + 31) / 32);
+  for (long long id0 = 0; id0 < n_pad; id0 += kMapIds) {
+    const int words = (int)((min((long long)kMapIds, n_pad - id0) + 31) / 32);
     __syncthreads();
     for (int k = tid; k < words; k += kStepBlock) s_map[k] = 0;
     __syncthreads();
     for (int k = tid; k < c; k += kStepBlock) {
-      const long long i = bucket[b + k] - first;
+      const long long i = bucket[b + k] - id0;
       if (i >= 0 && i < kMapIds) atomicOr(&s_map[i >> 5], 1u << (i & 31));
     }
     __syncthreads();
@@ -193,10 +210,10 @@ __global__ __launch_bounds__(kStepBlock) void k_raster_sort(RasterArgs a, const 
     int mine = 0;
     for (int w = w0; w < w1; ++w) mine += __popc(s_map[w]);
     int total;
-    int at = done + scan_block<kStepBlock>(mine, s_tmp, &total);
+    int o = done + scan_block<kStepBlock>(mine, s_tmp, &total);
     for (int w = w0; w < w1; ++w)
       for (unsigned m = s_map[w]; m; m &= m - 1)
-        a.out_id[b + at++] = dense_id(a, (int)first + 32 * w + __builtin_ctz(m));
+        a.out_id[b + o++] = dense_id(a, (int)id0 + 32 * w + __builtin_ctz(m));
     done += total;
   }
 }
@@ -213,9 +230,12 @@ hipError_t launch_raster_order(const RasterArgs& a, long long n_pad, int* hist, 
   hipError_t e = hipMemsetAsync(hist, 0, sizeof(int) * (size_t)span, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_raster_hist, dim3((unsigned)a.n_seg), dim3(256), 0, s, a, hist);
-  hipLaunchKernelGGL(k_raster_scan, dim3(1), dim3(kSmallBlock), 0, s, hist, span, off, cursor);
+  hipLaunchKernelGGL(k_raster_scan, dim3(1), dim3(kSmallBlock), 0, s, hist, span, off, cursor, a.head);
   hipLaunchKernelGGL(k_raster_scatter, dim3((unsigned)a.n_seg), dim3(256), 0, s, a, cursor, bucket);
-  hipLaunchKernelGGL(k_raster_sort, dim3((unsigned)span), dim3(kStepBlock), 0, s, a, off, bucket, n_pad);
+  constexpr long long kSteps = 1 << 22;      // workgroups of a launch: 2^32 threads are the most
+  for (long long first = 0; first < span; first += kSteps)
+    hipLaunchKernelGGL(k_raster_sort, dim3((unsigned)std::min(kSteps, span - first)), dim3(kStepBlock), 0, s, a, (int)first, off,
+                       bucket, n_pad);
   return hipGetLastError();
 }
 

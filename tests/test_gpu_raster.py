@@ -4,6 +4,7 @@ that a step's spikes by rank (up to 256) and through the id bitmap (one and
 several passes of 2^18 ids)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2111_04398_amd import mc, workloads
@@ -47,3 +48,47 @@ def test_every_neuron_fires_at_once(n):
     ref = one.spikes()[0]
     assert len(ref) >= 1 and len(s) == n * len(ref)
     assert np.array_equal(s, np.repeat(ref, n)) and np.array_equal(i, np.tile(np.arange(n, dtype=np.int32), len(ref)))
+
+
+def captured_spans(net, stream, steps):
+    """A graph that the caller captured, of one mc_simulate_noalloc call on the network's stream."""
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        net.simulate_noalloc(steps)
+    return graph
+
+
+@pytest.mark.parametrize("npw", [0, 256])
+def test_read_back_after_a_callers_graph_ran_more_steps_than_the_host_counted(npw):
+    """A program that captures a span and replays it: every replay's spikes come back, once, also
+    when none has been counted since the last read-back, and beyond 2,048 spikes."""
+    w = workloads.balanced()
+    stream = torch.cuda.Stream()
+    net, o = mc.Network(w, stream=stream.cuda_stream), oracle.Oracle(w.to_dict())
+    net.set_launch(scheme=1, block=512, neurons_per_wg=npw, steps_per_graph=0)
+    net.reserve(4000)
+    net.simulate_noalloc(100)
+    o.run(100)
+    assert len(net.spikes()[0]) == len(o.raster()[0])
+    graph = captured_spans(net, stream, 100)
+    for replays in (1, 1, 4, 1, 9):
+        for _ in range(replays):
+            with torch.cuda.stream(stream):
+                graph.replay()
+        before = len(o.raster()[0])
+        o.run(100 * replays)
+        (s, i), (os_, oi) = net.spikes(), o.raster()
+        assert len(os_) > before and np.array_equal(s, os_) and np.array_equal(i, oi), replays
+    assert len(net.spikes()[0]) == len(o.raster()[0])
+
+
+def test_read_back_of_more_segments_than_one_workgroup_sums():
+    """5,000 segments: always the long way, without and with spikes."""
+    w = lone_neuron(i_e=1000.0).replace(pop_size=[20000])
+    net = mc.Network(w)
+    net.set_launch(scheme=0, block=64, neurons_per_wg=4, steps_per_graph=0)
+    net.simulate(10)
+    assert len(net.spikes()[0]) == 0
+    net.simulate(38)
+    s, i = net.spikes()
+    assert np.array_equal(s, np.full(20000, 47, np.int32)) and np.array_equal(i, np.arange(20000, dtype=np.int32))
