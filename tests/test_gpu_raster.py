@@ -82,6 +82,24 @@ def test_read_back_after_a_callers_graph_ran_more_steps_than_the_host_counted(np
     assert len(net.spikes()[0]) == len(o.raster()[0])
 
 
+@pytest.mark.parametrize("n,steps", [(2047, 48), (2048, 48), (2049, 48), (255, 700), (256, 700), (257, 700),
+                                     (2**18, 48), (2**18 + 1, 48)])
+def test_read_back_at_the_limits_of_its_ways(n, steps):
+    """One burst of 2,047 to 2,049 spikes in all (one workgroup, or the long way); bursts of 255 to
+    257 spikes of which the long way reads more than 2,048 (by rank, or through the bitmap); a burst
+    on both sides of one bitmap pass."""
+    w = lone_neuron(i_e=1000.0)
+    o = oracle.Oracle(w.to_dict())
+    o.run(steps)
+    ref = o.raster()[0]
+    assert len(ref) == 1 if steps == 48 else len(ref) * n > 2048
+    net = mc.Network(w.replace(pop_size=[n]))
+    net.set_launch(scheme=0, block=256, neurons_per_wg=256, steps_per_graph=0)
+    net.simulate(steps)
+    s, i = net.spikes()
+    assert np.array_equal(s, np.repeat(ref, n)) and np.array_equal(i, np.tile(np.arange(n, dtype=np.int32), len(ref)))
+
+
 def test_read_back_of_more_segments_than_one_workgroup_sums():
     """5,000 segments: always the long way, without and with spikes."""
     w = lone_neuron(i_e=1000.0).replace(pop_size=[20000])
