@@ -129,7 +129,14 @@ typedef struct mc_config {
   void* alloc_ctx;
 } mc_config;
 
-/* Launch configuration of the simulation loop (see mc_set_launch). */
+/* Launch configuration of the simulation loop (see mc_set_launch).  The
+ * workgroups of a persistent launch (schemes 1 and 3) wait for one another, so
+ * all of them have to be on the GPU at once.  Persistent launches of several
+ * networks that overlap on one GPU (calls on different streams or from
+ * different threads) must therefore fit beside each other, in LDS (160 KB a
+ * compute unit) and registers (scheme 1: 12 wavefronts a compute unit, so at
+ * most 256 threads beside 512), or be serialized: launches that each hold a part of
+ * the GPU end with MC_ERR_TIMEOUT. */
 enum { MC_SCHEME_STEP_KERNELS = 0,   /* one kernel per step (update, then source-owner delivery with device
                                         atomics), replayed from a HIP graph */
        MC_SCHEME_PERSISTENT_LDS = 1,  /* one persistent kernel per chunk; near-future input held in LDS */
@@ -142,9 +149,9 @@ enum { MC_SCHEME_STEP_KERNELS = 0,   /* one kernel per step (update, then source
 typedef struct mc_launch {
   uint32_t struct_size;
   int32_t scheme;
-  int32_t block;                 /* threads per workgroup: 64..1024, multiple of 64 (persistent: where every
-                                    workgroup has a compute unit to itself, further wavefronts, up to 768
-                                    threads, only deliver) */
+  int32_t block;                 /* threads per workgroup: 64..1024, multiple of 64 (persistent: where a
+                                    workgroup's LDS window leaves no room on its compute unit for another
+                                    launch's, further wavefronts, up to 768 threads, only deliver) */
   int32_t neurons_per_wg;        /* neurons updated by one workgroup: multiple of 4, <= 4*block, <= 1024
                                     (persistent: <= block; target owner: the targets of one delivery block,
                                     its update kernel takes 4*block neurons, at most 1024; buckets: <= min(4092,

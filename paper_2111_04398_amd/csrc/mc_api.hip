@@ -512,16 +512,21 @@ int validate_launch(const mc_net* n, const mc_launch& l) {
 }
 
 // Threads per workgroup of the persistent kernel: the launch configuration's
-// block, and, where every workgroup has a compute unit to itself, wavefronts up
-// to kPersistThreads that only deliver.  The delivery of a burst is bound by the
+// block, and, where every workgroup has a compute unit to itself and its window
+// has taken all the LDS there, wavefronts up to kPersistThreads that only
+// deliver.  The delivery of a burst is bound by the
 // loads in flight: read back in a loop of its own, the rows of 120,000 spikes of
 // the full microcircuit took 16.9 ns each with 7 wavefronts per compute unit and
 // 10.4 ns with 14; in the step loop 12 instead of 8 take 3.98 instead of 4.31 us
-// per step.  Workgroups that share a compute unit keep their block: wavefronts
-// are placed SIMD by SIMD, and two workgroups of six at three per SIMD need not
-// fit although the unit has room for twelve.
-int persist_threads(const mc_net* n, int g, int block) {
-  return g <= n->n_cu ? std::max(block, kPersistThreads) : block;
+// per step.  A smaller window leaves LDS that a launch of another network on
+// another stream may be counting on, and twelve wavefronts would leave it no
+// registers: such a launch keeps its block (balanced network 25.8 -> 26.1 ms per
+// 10,000 steps; microcircuit at scale 0.1: no difference).  Workgroups that share
+// a compute unit keep theirs too: wavefronts are placed SIMD by SIMD, and two
+// workgroups of six at three per SIMD need not fit although the unit has room
+// for twelve.
+int persist_threads(const mc_net* n, int g, int block, int dl) {
+  return g <= n->n_cu && dl < kPersistMaxWindow ? std::max(block, kPersistThreads) : block;
 }
 
 // Shape of the persistent scheme: G co-resident workgroups, workgroup g owning
@@ -552,11 +557,11 @@ int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, std::v
   const int per_cu = (g + n->n_cu - 1) / n->n_cu;
   const size_t budget = (size_t)n->lds_max / per_cu;
   if (stat + base + 2 * (size_t)b * 8 > budget) return set_error(MC_ERR_RANGE, "LDS too small for the persistent scheme");
-  const int dl = (int)std::min<size_t>(102, (budget - stat - base) / ((size_t)b * 8));
+  const int dl = (int)std::min<size_t>(kPersistMaxWindow, (budget - stat - base) / ((size_t)b * 8));
   const size_t lds = persist_lds_bytes(g, b, dl);
   HIP_TRY(persist_set_lds_limit(lds));
   int occ = 0;
-  HIP_TRY(persist_occupancy(persist_threads(n, g, l.block), lds, &occ));
+  HIP_TRY(persist_occupancy(persist_threads(n, g, l.block, dl), lds, &occ));
   // (workgroups that share a compute unit: two wavefronts per SIMD at most, which fit however they are placed)
   if (occ < 1 || g > n->n_cu * occ || (per_cu > 1 && per_cu * l.block > 512))
     return set_error(MC_ERR_RANGE, "persistent workgroups would not all be co-resident");
@@ -707,7 +712,7 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     (void)hipGraphExecDestroy(n->graph);
     n->graph = nullptr;
   }
-  if (l.scheme == MC_SCHEME_PERSISTENT_LDS) n->pthreads = persist_threads(n, G, l.block);
+  if (l.scheme == MC_SCHEME_PERSISTENT_LDS) n->pthreads = persist_threads(n, G, l.block, DL);
   if (shape_changed || !n->d_raster) {
     // the old shape's buffers go first: a failure from here on leaves no
     // consistent shape, so it marks the handle failed
