@@ -680,6 +680,29 @@ int setup_owner(mc_net* n, int targets, int max_targets) {
   return MC_OK;
 }
 
+// Tables of the persistent scheme for G workgroups.
+struct PersistTables {
+  unsigned* off = nullptr;
+  unsigned long long *pk = nullptr, *flags = nullptr;
+  int* bstart = nullptr;
+};
+
+// Allocates them beside what the network holds; the packed rows, one place per
+// synapse whatever the shape, are taken over from an earlier shape.  On failure
+// nothing has changed.
+int alloc_persist(mc_net* n, int G, PersistTables* t) {
+  int rc = dev_alloc(n->alloc, &t->off, (size_t)n->n_pad * (G + 1));
+  t->pk = n->d_pk;
+  if (rc == MC_OK && !t->pk) rc = dev_alloc(n->alloc, &t->pk, (size_t)n->h.M);
+  if (rc == MC_OK) rc = dev_alloc(n->alloc, &t->flags, window_flag_words(G));
+  if (rc == MC_OK) rc = dev_alloc(n->alloc, &t->bstart, (size_t)G + 1);
+  if (rc == MC_OK) return MC_OK;
+  dev_free(n->alloc, t->off); dev_free(n->alloc, t->flags); dev_free(n->alloc, t->bstart);
+  if (!n->d_pk) dev_free(n->alloc, t->pk);
+  *t = PersistTables{};
+  return rc;
+}
+
 int apply_launch(mc_net* n, const mc_launch& l) {
   int rc = validate_launch(n, l);
   if (rc != MC_OK) return rc;
@@ -712,23 +735,37 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     (void)hipGraphExecDestroy(n->graph);
     n->graph = nullptr;
   }
-  if (l.scheme == MC_SCHEME_PERSISTENT_LDS) n->pthreads = persist_threads(n, G, l.block, DL);
+  const int pthreads = l.scheme == MC_SCHEME_PERSISTENT_LDS ? persist_threads(n, G, l.block, DL) : 0;
   if (shape_changed || !n->d_raster) {
-    // the old shape's buffers go first: a failure from here on leaves no
-    // consistent shape, so it marks the handle failed
+    // the old shape's buffers go before the new ones are complete: a failure in
+    // between leaves no consistent shape, so it marks the handle failed
     struct FailGuard {
       mc_net* n; bool armed = true;
       ~FailGuard() { if (armed) n->failed = true; }
     } guard{n};
     if ((rc = drain(n)) != MC_OK) return rc;
     if ((rc = fold_counters(n)) != MC_OK) return rc;
+    PersistTables t;
+    if (l.scheme == MC_SCHEME_PERSISTENT_LDS && (rc = alloc_persist(n, G, &t)) != MC_OK) {
+      // The packed rows are nearly as large as the store.  Without the old
+      // shape's raster there may be room; if not, the old shape stays.
+      release_recording(n);
+      if ((rc = alloc_persist(n, G, &t)) != MC_OK && n->launch.scheme == MC_SCHEME_PERSISTENT_LDS) {
+        dev_free(n->alloc, n->d_off);          // from one persistent shape to another only this is large: it goes first
+        rc = alloc_persist(n, G, &t);
+        if (rc != MC_OK) return rc;
+      }
+      if (rc != MC_OK) {
+        const std::string msg = g_last_error;
+        guard.armed = false;
+        const int back = setup_recording(n, n->cap_steps);
+        return back == MC_OK ? set_error(rc, msg + " (the launch configuration is left as it was)") : back;
+      }
+    }
     release_recording(n);   // sized for the old shape
     if (l.scheme == MC_SCHEME_PERSISTENT_LDS) {
-      dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_pk); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_bstart);
-      if ((rc = dev_alloc(n->alloc, &n->d_off, (size_t)n->n_pad * (G + 1))) != MC_OK) return rc;
-      if ((rc = dev_alloc(n->alloc, &n->d_pk, (size_t)n->h.M)) != MC_OK) return rc;
-      if ((rc = dev_alloc(n->alloc, &n->d_flags, window_flag_words(G))) != MC_OK) return rc;
-      if ((rc = dev_alloc(n->alloc, &n->d_bstart, (size_t)G + 1)) != MC_OK) return rc;
+      dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_bstart);
+      n->d_off = t.off; n->d_pk = t.pk; n->d_flags = t.flags; n->d_bstart = t.bstart;
       HIP_TRY(hipMemcpy(n->d_bstart, bs.data(), sizeof(int) * (G + 1), hipMemcpyHostToDevice));
       n->bstart_host = bs;
       HIP_TRY(hipMemsetAsync(n->d_flags, 0, sizeof(unsigned long long) * window_flag_words(G), n->stream));
@@ -759,11 +796,13 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     // the LDS-window scheme's shape (its tables are rebuilt whenever it is set again)
     const bool lds_scheme = l.scheme == MC_SCHEME_PERSISTENT_LDS;
     n->pG = lds_scheme ? G : 0; n->pB = lds_scheme ? B : 0; n->pDL = lds_scheme ? DL : 0;
+    n->pthreads = pthreads;
     n->launch = l;
     guard.armed = false;   // setup_recording keeps the handle usable on its own failures where it can
     if ((rc = setup_recording(n, std::max<int64_t>(n->cap_steps, 4096))) != MC_OK) return rc;
   }
   n->launch = l;
+  n->pthreads = pthreads;
   return MC_OK;
 }
 

@@ -1,0 +1,62 @@
+"""Device memory of a network: what happens when it runs out, and what goes back."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2111_04398_amd import mc, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+class Hooks:
+    """Allocator hooks on torch's caching allocator that refuse the sizes in `refuse`."""
+
+    def __init__(self):
+        self.live, self.refuse, self.refused = {}, set(), 0
+
+    def alloc(self, nbytes):
+        if nbytes in self.refuse:
+            self.refused += 1
+            return None
+        p = torch.cuda.caching_allocator_alloc(nbytes)
+        self.live[p] = nbytes
+        return p
+
+    def free(self, ptr):
+        del self.live[ptr]
+        torch.cuda.caching_allocator_delete(ptr)
+
+    def network(self, w):
+        return mc.Network(w, allocator=(self.alloc, self.free))
+
+
+def same_spikes(a, b):
+    (s0, i0), (s1, i1) = a.spikes(), b.spikes()
+    return len(s0) > 0 and np.array_equal(s0, s1) and np.array_equal(i0, i1)
+
+
+@pytest.mark.parametrize("scheme,block,npw", [(0, 256, 256), (2, 256, 256), (3, 256, 0)])
+def test_without_memory_for_the_packed_rows_the_network_keeps_its_launch(scheme, block, npw):
+    """The persistent scheme's copy of the store (8 B per synapse) does not fit: mc_set_launch says so, and
+    the network goes on with the launch it had; the autotuner passes over the scheme."""
+    w = workloads.balanced()
+    hooks = Hooks()
+    net, twin = hooks.network(w), mc.Network(w)
+    for n in (net, twin):
+        n.set_launch(scheme=scheme, block=block, neurons_per_wg=npw, steps_per_graph=100)
+        n.simulate(150)
+    hooks.refuse = {8 * net.M}
+    before = dict(hooks.live)
+    with pytest.raises(mc.MCError) as e:
+        net.set_launch(scheme=1, block=512, neurons_per_wg=0, steps_per_graph=100)
+    assert e.value.code == -3 and hooks.refused >= 1
+    assert sorted(hooks.live.values()) == sorted(before.values())
+    for n in (net, twin):
+        n.simulate(150)
+    assert same_spikes(net, twin) and net.counters()["events"] == twin.counters()["events"]
+    net.tune(200)
+    for n in (net, twin):
+        n.simulate(150)
+    assert same_spikes(net, twin)
+    net.close()
+    assert not hooks.live
