@@ -763,6 +763,9 @@ int apply_launch(mc_net* n, const mc_launch& l) {
       }
     }
     release_recording(n);   // sized for the old shape
+    if (l.scheme != MC_SCHEME_PERSISTENT_LDS) {   // (setting the persistent scheme again makes its tables anew)
+      dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_pk); dev_free(n->alloc, n->d_bstart);
+    }
     if (l.scheme == MC_SCHEME_PERSISTENT_LDS) {
       dev_free(n->alloc, n->d_off); dev_free(n->alloc, n->d_flags); dev_free(n->alloc, n->d_bstart);
       n->d_off = t.off; n->d_pk = t.pk; n->d_flags = t.flags; n->d_bstart = t.bstart;

@@ -60,3 +60,20 @@ def test_without_memory_for_the_packed_rows_the_network_keeps_its_launch(scheme,
     assert same_spikes(net, twin)
     net.close()
     assert not hooks.live
+
+
+def test_packed_rows_are_kept_where_they_are_used_and_go_back_elsewhere():
+    w = workloads.balanced()
+    hooks = Hooks()
+    net, twin = hooks.network(w), mc.Network(w)
+    rows = 8 * net.M
+
+    def held():
+        return sum(1 for b in hooks.live.values() if b == rows)
+
+    for scheme, npw, want in ((1, 0, 1), (1, 64, 1), (0, 256, 0), (1, 64, 1), (3, 0, 0), (1, 0, 1), (2, 256, 0)):
+        net.set_launch(scheme=scheme, block=256, neurons_per_wg=npw, steps_per_graph=100)
+        assert held() == want, (scheme, npw)
+        for n in (net, twin):
+            n.simulate(120)
+    assert same_spikes(net, twin)
