@@ -348,6 +348,10 @@ int64_t spike_bound(int64_t neurons, int64_t steps, int ref) {
   return neurons * ((steps + ref) / (ref + 1));
 }
 
+// Read-back buffers up to this size are kept for the next one (8 million
+// spikes, 13 s of the full microcircuit); larger ones go back after use.
+constexpr size_t kKeepReadBack = 64u << 20;
+
 // Pinned memory for a read-back of `spikes` spikes.
 int reserve_spikes(mc_net* n, int64_t spikes) {
   if (n->h_spk && n->spk_cap >= spikes) return MC_OK;
@@ -423,6 +427,15 @@ int drain(mc_net* n, hipEvent_t upto = nullptr) {
   } catch (const std::bad_alloc&) {
     n->failed = true;
     return set_error(MC_ERR_OOM, "host allocation of the spike list failed");
+  }
+  if (sizeof(int) * 2 * (size_t)n->spk_cap > kKeepReadBack) {
+    (void)hipHostFree(n->h_spk);
+    n->h_spk = nullptr;
+    n->spk_cap = 0;
+  }
+  if (sizeof(int) * (size_t)n->rwork_cap > kKeepReadBack) {
+    dev_free(n->alloc, n->d_rwork);
+    n->rwork_cap = 0;
   }
   n->steps_since_drain = 0;
   return MC_OK;

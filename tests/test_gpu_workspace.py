@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2111_04398_amd import mc, workloads
+from test_oracle_dynamics import lone_neuron
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +78,18 @@ def test_packed_rows_are_kept_where_they_are_used_and_go_back_elsewhere():
         for n in (net, twin):
             n.simulate(120)
     assert same_spikes(net, twin)
+
+
+def test_buffers_of_a_long_read_back_go_back():
+    """17 million spikes at once (a burst of a million neurons every 68 steps): 100 MB of scratch."""
+    n = 1_000_000
+    hooks = Hooks()
+    net = hooks.network(lone_neuron(i_e=1000.0).replace(pop_size=[n]))
+    net.set_launch(scheme=0, block=256, neurons_per_wg=1024, steps_per_graph=0)
+    net.reserve(1136)
+    before = sorted(hooks.live.values())
+    net.simulate(1136)
+    s, i = net.spikes()
+    assert np.array_equal(s, np.repeat(np.arange(47, 1136, 68, dtype=np.int32), n)) and np.array_equal(i[-n:], i[:n])
+    assert np.array_equal(i[:n], np.arange(n, dtype=np.int32))
+    assert sorted(hooks.live.values()) == before
