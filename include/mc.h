@@ -201,9 +201,9 @@ int mc_build_network(const mc_config* cfg, mc_net** out);
  * trajectory bit for bit.  Errors: STATE (host-only or failed handle), HIP,
  * OOM (raster growth).  Test hook: the environment variable
  * MC_PERSIST_LIST_CAP = k makes the persistent scheme, in the steps that
- * mc_profile_phases runs, hold at most k spike ids (but always a workgroup's
- * own targets) in its LDS queue, so that its poller has to wait for room;
- * results are unchanged. */
+ * mc_profile_phases runs, hold at most k spike ids (but 32 at least, and as
+ * many as a workgroup has targets) in its LDS queue, so that its poller has
+ * to wait for room; results are unchanged. */
 int mc_simulate(mc_net* net, int64_t steps);
 
 /* For callers that cannot allocate memory (code under HIP graph capture,

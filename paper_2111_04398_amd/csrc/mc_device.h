@@ -90,7 +90,8 @@ struct PersistArgs {
   long long wait_ticks;        // longest wait for one step's records, in wall_clock64 ticks (then: error bit 2)
   unsigned long long* phase;   // optional [G*8]: summed wall_clock64 ticks per phase (nullptr: off)
   // ids the queue holds at most (0: its capacity); a smaller value is a test
-  // hook that makes the poller wait for room (phase-timing instance only)
+  // hook that makes the poller wait for room, in a queue of fewer slots
+  // (phase-timing instance only)
   int list_cap;
 };
 constexpr int kPersistFlagStride = 8;

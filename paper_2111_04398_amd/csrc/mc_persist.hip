@@ -155,12 +155,13 @@ __device__ __forceinline__ unsigned uni(unsigned x) { return (unsigned)__builtin
 // which it issues them; the fence keeps the compiler to it and costs nothing.
 struct IdQueue {
   const unsigned* slots;
+  unsigned mask;                              // slots - 1
   unsigned* s_head;
   int lane;
   unsigned id;
   __device__ __forceinline__ unsigned head() { return uni(lds_rlx(s_head)); }
   __device__ __forceinline__ void read(unsigned h) {
-    id = lds_rlx(&slots[(h + (unsigned)lane) & (kQueue - 1)]);
+    id = lds_rlx(&slots[(h + (unsigned)lane) & mask]);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
   __device__ __forceinline__ unsigned take(unsigned h, unsigned to) {
@@ -244,9 +245,14 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
   const bool drifts = p.i_e != 0.0;
   const long long jext_q = own_v(p.jext_q);
   const int ref_steps = own_v(p.ref_steps);
-  // the queue's capacity (a test hook makes it smaller, in the phase-timing
-  // instance only; a record's ids always fit)
-  const unsigned qcap = (kTime && a.list_cap > 0) ? (unsigned)min(max(a.list_cap, B), kQueue) : (unsigned)kQueue;
+  // the queue's capacity and slots (a test hook makes them fewer, in the
+  // phase-timing instance only; what the poller puts in at once always fits:
+  // the ids of a long record, or of the short records that a lane polls)
+  unsigned qcap = kQueue, qmask = kQueue - 1;
+  if (kTime && a.list_cap > 0) {
+    qcap = (unsigned)min(max(a.list_cap, max(B, kW0Ids * kPoll)), kQueue);
+    qmask = (1u << (32 - __builtin_clz(qcap - 1))) - 1;
+  }
 
   for (int k = tid; k < p.n_pops * kTableLen; k += nthr) s_table[k] = p.table[k];
   for (int k = tid; k < DL * B; k += nthr) acc[k] = 0;
@@ -695,7 +701,7 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
             const unsigned b = (unsigned)((lane + 64 * k) * B) | qtag;   // ids < 2^18, with a local index too: no carry
 #pragma unroll
             for (int e = 0; e < kW0Ids; ++e)
-              if ((unsigned)e < c) s_q[(o + (unsigned)e) & (kQueue - 1)] = b + ((unsigned)(w0[k] >> (9 * e)) & 0x1FFu);
+              if ((unsigned)e < c) s_q[(o + (unsigned)e) & qmask] = b + ((unsigned)(w0[k] >> (9 * e)) & 0x1FFu);
             o += c;
           }
         }
@@ -742,7 +748,7 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
               if (ok) {
                 unsigned o = tail + (unsigned)(x - __popcll(mm));
                 const unsigned b = ((unsigned)((own[q] + 64 * k) * B) | qtag) + (unsigned)(kMapBits * L);
-                for (; mm; mm &= mm - 1) s_q[o++ & (kQueue - 1)] = b + (unsigned)__builtin_ctzll(mm);
+                for (; mm; mm &= mm - 1) s_q[o++ & qmask] = b + (unsigned)__builtin_ctzll(mm);
               }
               const unsigned long long acc_m = __ballot(ok);
 #pragma unroll
@@ -778,7 +784,7 @@ __global__ __launch_bounds__(kPersistThreads) void k_persist(DevNet p, PersistAr
       // later steps' ids are not what an update waits for: it leaves them to
       // the other wavefronts unless many pile up (a burst)
       if (limited && (int)(t - limit) <= nw * per) t = limit;
-      IdQueue queue{s_q, &s_head, lane, 0u};
+      IdQueue queue{s_q, qmask, &s_head, lane, 0u};
       const unsigned c = claim_ids(queue, t, (unsigned)per, (unsigned)nw);
       if (c > 0) {
         const long long tq = kTime ? wall_clock64() : 0;
