@@ -98,11 +98,14 @@ void dev_free(const Alloc& A, T*& p) {
   p = nullptr;
 }
 
-// Device buffers of one adjoint call, freed on every exit path.
+// Device buffers of one adjoint call, freed on every exit path -- also one by
+// an error or an exception with kernels still queued, which have to end first:
+// memory that goes back to an allocator hook may be handed out at once.
 struct AdjBuffers {
   const Alloc& A;
+  hipStream_t stream;
   std::vector<void*> ptrs;
-  explicit AdjBuffers(const Alloc& a) : A(a) {}
+  AdjBuffers(const Alloc& a, hipStream_t s) : A(a), stream(s) {}
   template <class T>
   int alloc(T** p, size_t count) {
     int rc = dev_alloc(A, p, count);
@@ -110,6 +113,7 @@ struct AdjBuffers {
     return rc;
   }
   ~AdjBuffers() {
+    if (hipStreamSynchronize(stream) != hipSuccess) (void)hipGetLastError();
     for (void* p : ptrs) dev_free(A, p);
   }
 };
@@ -1886,7 +1890,7 @@ static int run_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double
   int R = 1;
   while (R < Kc + 101) R <<= 1;
   int rc;
-  AdjBuffers B(n->alloc);
+  AdjBuffers B(n->alloc, n->stream);
   double *ck_y = nullptr, *ck_I = nullptr;
   int32_t* ck_r = nullptr;
   long long* ck_ring = nullptr;
@@ -2131,7 +2135,6 @@ int mc_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double* loss) 
   try {
     return run_adjoint(n, a, grad, loss);
   } catch (const std::bad_alloc&) {            // the work lists of the reverse pass
-    if (n->stream) (void)hipStreamSynchronize(n->stream);
     n->failed = true;
     return set_error(MC_ERR_OOM, "host allocation failed in the adjoint");
   }

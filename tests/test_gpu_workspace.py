@@ -28,7 +28,7 @@ class Hooks:
         torch.cuda.caching_allocator_delete(ptr)
 
     def network(self, w):
-        return mc.Network(w, allocator=(self.alloc, self.free))
+        return mc.Network(w, allocator=(lambda nbytes: self.alloc(nbytes), lambda ptr: self.free(ptr)))
 
 
 def same_spikes(a, b):
@@ -93,3 +93,36 @@ def test_buffers_of_a_long_read_back_go_back():
     assert np.array_equal(s, np.repeat(np.arange(47, 1136, 68, dtype=np.int32), n)) and np.array_equal(i[-n:], i[:n])
     assert np.array_equal(i[:n], np.arange(n, dtype=np.int32))
     assert sorted(hooks.live.values()) == before
+
+
+@pytest.mark.parametrize("mode", [mc.ADJ_INPUT_RECORD, mc.ADJ_INPUT_REPLAY])
+def test_buffers_of_an_adjoint_that_fails_go_back_after_its_kernels(mode):
+    """No memory for the reverse pass's lists, the last allocation of the call: forward and recompute are queued
+    by then, and end before any buffer goes back to the allocator."""
+    w = workloads.microcircuit(scale=0.05)
+    hooks, idle = Hooks(), []
+    net = hooks.network(w)
+    net.set_launch(scheme=1, block=512, neurons_per_wg=0, steps_per_graph=0)
+    net.reserve(4096)
+    stream = torch.cuda.ExternalStream(net.stream())
+    free, alloc = hooks.free, hooks.alloc
+    sizes = []
+    hooks.alloc = lambda nbytes: sizes.append(nbytes) or alloc(nbytes)
+    hooks.free = lambda ptr: (idle.append(stream.query()), free(ptr))
+    fresh = net.save_state()
+    grad = torch.empty(net.M, dtype=torch.float64, device="cuda")
+
+    def adjoint():
+        net.load_state(fresh)
+        return net.adjoint(2000, 2000, -58.0, False, grad.data_ptr(), input_mode=mode)
+
+    loss = adjoint()
+    assert adjoint() == loss
+    want = grad.clone()
+    hooks.refuse = {sizes[-1]}
+    del idle[:]
+    with pytest.raises(mc.MCError) as e:
+        adjoint()
+    assert e.value.code == -3 and hooks.refused == 1 and len(idle) >= 8 and all(idle)
+    hooks.refuse = set()
+    assert adjoint() == loss and torch.equal(grad, want)
