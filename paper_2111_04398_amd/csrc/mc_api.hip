@@ -1922,8 +1922,11 @@ static int run_adjoint(mc_net* n, const mc_adjoint_config* a, void* grad, double
   if ((rc = B.alloc(&mismatch, 1)) != MC_OK) return rc;
   loss_part = carry + 2 * st;
   if (adj_gather_ranged(st) && !n->d_adj_rb &&
-      dev_alloc(n->alloc, &n->d_adj_rb, (size_t)n->n_pad * (kAdjRanges + 1)) == MC_OK)
-    HIP_TRY(launch_adj_bounds(n->d_row_ptr, n->d_tgt, n->n_pad, n->d_adj_rb, n->stream));
+      dev_alloc(n->alloc, &n->d_adj_rb, (size_t)n->n_pad * (kAdjRanges + 1)) == MC_OK) {
+    const hipError_t e = launch_adj_bounds(n->d_row_ptr, n->d_tgt, n->n_pad, n->d_adj_rb, n->stream);
+    if (e != hipSuccess) dev_free(n->alloc, n->d_adj_rb);   // (a later call must not take it for made)
+    HIP_TRY(e);
+  }
   const bool ranged = n->d_adj_rb != nullptr;  // (without the memory for it, the plain gather)
   HIP_TRY(hipMemsetAsync(carry, 0, sizeof(double) * 3 * st, n->stream));
   HIP_TRY(hipMemsetAsync(seg_count, 0, sizeof(unsigned long long) * nseg, n->stream));
