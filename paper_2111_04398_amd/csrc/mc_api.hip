@@ -298,12 +298,6 @@ struct mc_net {
     const int b = inst_of(dense);
     return dense - h.inst_off[b] + inst_off_pad[b];
   }
-  int64_t dense_of(int64_t padded) const {
-    const int b = (int)(std::upper_bound(inst_off_pad.begin(), inst_off_pad.end(), padded) - inst_off_pad.begin()) - 1;
-    const int64_t local = padded - inst_off_pad[b];
-    if (local >= h.inst_off[b + 1] - h.inst_off[b]) return -1;
-    return h.inst_off[b] + local;
-  }
 };
 
 namespace {
@@ -569,13 +563,13 @@ int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, std::v
     return set_error(MC_ERR_RANGE, "persistent scheme needs workgroups <= 2 x threads per workgroup and <= 512");
   size_t stat = 0;
   HIP_TRY(persist_static_lds(&stat));
-  const size_t base = persist_lds_bytes(g, b, 0);
+  const size_t base = persist_lds_bytes(b, 0);
   // workgroups that must share a compute unit divide its LDS
   const int per_cu = (g + n->n_cu - 1) / n->n_cu;
   const size_t budget = (size_t)n->lds_max / per_cu;
   if (stat + base + 2 * (size_t)b * 8 > budget) return set_error(MC_ERR_RANGE, "LDS too small for the persistent scheme");
   const int dl = (int)std::min<size_t>(kPersistMaxWindow, (budget - stat - base) / ((size_t)b * 8));
-  const size_t lds = persist_lds_bytes(g, b, dl);
+  const size_t lds = persist_lds_bytes(b, dl);
   HIP_TRY(persist_set_lds_limit(lds));
   int occ = 0;
   HIP_TRY(persist_occupancy(persist_threads(n, g, l.block, dl), lds, &occ));
@@ -1543,7 +1537,7 @@ int mc_profile_phases(mc_net* n, int64_t steps, double* us) {
   for (size_t k = 0; k < h.size(); ++k) n->phase_wg[k] = (k % 8 == 7) ? 0.0 : (double)h[k] * tick_us / (double)steps;
   us[5] = 0;
   for (int k = 0; k < 5; ++k) { us[k] = acc[k] * norm; us[5] += us[k]; }
-  us[6] = acc[5] * norm;   // drive + pending delivery of wavefront 0 while waiting
+  us[6] = acc[5] * norm;   // drive of the next steps
   us[7] = acc[6] * norm;   // polling of the first poller thread
   return MC_OK;
 }

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kBucketMaxBlock) void k_bucket(DevNet p, BucketArgs
   };
   auto publish = [&](long long m, uint64_t mask) {   // compaction, record of step m, raster
     // slots in any order (delivery sums integers; the raster of a step is
-    // ordered on the host): a lane-prefix of the spike counts, one LDS atomic
+    // ordered when it is read back): a lane-prefix of the spike counts, one LDS atomic
     // per wavefront for its base
     const int c = __popcll(mask);
     int x = c;

@@ -115,7 +115,7 @@ constexpr int kPersistMaxB = 512;       // owned targets per workgroup (one per 
 constexpr int kPersistMaxBlock = 512;   // threads per workgroup of a launch configuration
 constexpr int kPersistMaxWindow = 102;  // steps of input in LDS (delays up to this - 2 go there: all of them)
 constexpr int kPersistThreads = 768;   // threads of a workgroup alone on its compute unit: 168 VGPRs per lane
-size_t persist_lds_bytes(int G, int B, int DL);
+size_t persist_lds_bytes(int B, int DL);
 // Fills the packed rows and their sub-row bounds for G workgroups of B targets.
 hipError_t launch_pack_rows(const int64_t* row_ptr, const int32_t* tgt, const int32_t* wq, const uint8_t* dly,
                             long long n_pad, int G, int B, unsigned* off, unsigned long long* pk, hipStream_t s);
@@ -125,7 +125,6 @@ hipError_t persist_set_lds_limit(size_t lds);
 hipError_t launch_persist(const DevNet& p, const PersistArgs& a, int steps, int threads, hipStream_t s);
 // Scratch of the allocation-free entry point (mc_noalloc.hip): the spike
 // records of this device (room for 512 workgroups); and a record clear by kernel.
-size_t noalloc_record_words();
 hipError_t noalloc_scratch(int device, unsigned long long** records);
 hipError_t launch_clear_records(unsigned long long* records, size_t words, hipStream_t s);
 

@@ -32,8 +32,6 @@ __global__ void k_fill_u64(unsigned long long* p, long long n, unsigned long lon
 
 }  // namespace
 
-size_t noalloc_record_words() { return kScratchRecordWords; }
-
 // Device address of this device's scratch, looked up on the first call for
 // the device (which must be current) and kept.
 hipError_t noalloc_scratch(int device, unsigned long long** records) {

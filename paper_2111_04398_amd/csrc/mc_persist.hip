@@ -204,7 +204,7 @@ __device__ __forceinline__ uint32_t drive_counts(long long n, uint32_t qlocal, u
 }  // namespace
 
 // LDS (dynamic): acc[DL*B] i64 | fbits[128*BW] u32 | s_q[kQueue] u32 |
-//                s_units[16][kUnits] 16 bytes (B is a multiple of 4: all aligned)
+//                s_units[kPersistThreads / 64][kUnits] 16 bytes (B is a multiple of 4: all aligned)
 // kRec: the adjoint's forward recording (input x and state checkpoints);
 // kTime: phase timestamps.  Plain simulation runs the instance with neither
 // (fewer registers).  kPoll: producers polled per lane (4 when G <= 256: a
@@ -1004,8 +1004,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_rows(const int64_t* row_ptr
   }
 }
 
-size_t persist_lds_bytes(int G, int B, int DL) {
-  (void)G;
+size_t persist_lds_bytes(int B, int DL) {
   const int BW = (B + 31) / 32;
   return (size_t)DL * B * 8 + (size_t)128 * BW * 4 + (size_t)kQueue * 4 + (size_t)(kPersistThreads / 64) * kUnits * 16;
 }
@@ -1047,7 +1046,7 @@ static void launch_persist_as(const DevNet& p, const PersistArgs& a, int steps, 
 }
 
 hipError_t launch_persist(const DevNet& p, const PersistArgs& a, int steps, int block, hipStream_t s) {
-  const size_t lds = persist_lds_bytes(a.G, a.B, a.DL);
+  const size_t lds = persist_lds_bytes(a.B, a.DL);
   const bool rec = p.xrec != nullptr || p.ck_y != nullptr, tim = a.phase != nullptr;
   if (rec && tim) launch_persist_as<true, true>(p, a, steps, block, lds, s);
   else if (rec) launch_persist_as<true, false>(p, a, steps, block, lds, s);
