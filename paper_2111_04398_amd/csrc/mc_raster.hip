@@ -84,12 +84,23 @@ __global__ __launch_bounds__(kSmallBlock) void k_raster_small(RasterArgs a) {
     int* range = reinterpret_cast<int*>(s_key + 1);
     if (tid == 0) { sum[0] = 0; range[0] = 0x7FFFFFFF; range[1] = -1; }
     __syncthreads();
-    if (mine) atomicAdd(sum, (unsigned long long)mine);
+    int first = 0x7FFFFFFF, last = -1;
     for (int k = tid * per; k < min((tid + 1) * per, a.n_seg); ++k) {
       const long long c = a.cnt[k];        // (a segment is ordered by step)
       if (c == 0) continue;
-      atomicMin(&range[0], a.raster[(size_t)k * a.cap].x);
-      atomicMax(&range[1], a.raster[(size_t)k * a.cap + c - 1].x);
+      first = min(first, a.raster[(size_t)k * a.cap].x);
+      last = max(last, a.raster[(size_t)k * a.cap + c - 1].x);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      mine += __shfl_xor(mine, o, 64);
+      first = min(first, __shfl_xor(first, o, 64));
+      last = max(last, __shfl_xor(last, o, 64));
+    }
+    if ((tid & 63) == 0) {
+      atomicAdd(sum, (unsigned long long)mine);
+      atomicMin(&range[0], first);
+      atomicMax(&range[1], last);
     }
     __syncthreads();
     if (tid == 0) {
