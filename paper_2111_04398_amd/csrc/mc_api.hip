@@ -523,21 +523,22 @@ int validate_launch(const mc_net* n, const mc_launch& l) {
 }
 
 // Threads per workgroup of the persistent kernel: the launch configuration's
-// block, and, where every workgroup has a compute unit to itself and its window
-// has taken all the LDS there, wavefronts up to kPersistThreads that only
-// deliver.  The delivery of a burst is bound by the
+// block, and, where every workgroup has a compute unit to itself and leaves no
+// LDS there for another's, wavefronts up to kPersistThreads that only deliver.
+// The delivery of a burst is bound by the
 // loads in flight: read back in a loop of its own, the rows of 120,000 spikes of
 // the full microcircuit took 16.9 ns each with 7 wavefronts per compute unit and
 // 10.4 ns with 14; in the step loop 12 instead of 8 take 3.98 instead of 4.31 us
 // per step.  A smaller window leaves LDS that a launch of another network on
 // another stream may be counting on, and twelve wavefronts would leave it no
-// registers: such a launch keeps its block (balanced network 25.8 -> 26.1 ms per
-// 10,000 steps; microcircuit at scale 0.1: no difference).  Workgroups that share
+// registers: such a launch keeps its block (balanced network 2.58 -> 2.61 us per
+// step; microcircuit at scale 0.1: no difference, at 0.2 2.69 -> 2.75, at 0.4 2.92
+// -> 3.04).  Workgroups that share
 // a compute unit keep theirs too: wavefronts are placed SIMD by SIMD, and two
 // workgroups of six at three per SIMD need not fit although the unit has room
 // for twelve.
-int persist_threads(const mc_net* n, int g, int block, int dl) {
-  return g <= n->n_cu && dl < kPersistMaxWindow ? std::max(block, kPersistThreads) : block;
+int persist_threads(const mc_net* n, int g, int block, size_t free_lds) {
+  return g <= n->n_cu && free_lds < kPersistLeastLds ? std::max(block, kPersistThreads) : block;
 }
 
 // Shape of the persistent scheme: G co-resident workgroups, workgroup g owning
@@ -547,7 +548,7 @@ int persist_threads(const mc_net* n, int g, int block, int dl) {
 // neurons_per_wg = 0: one workgroup per compute unit.  (Blocks sized to
 // equalise the expected synaptic input per workgroup were measured slower on
 // the full microcircuit: the larger blocks leave fewer delay steps in LDS.)
-int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, std::vector<int>& bs) {
+int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, int* threads, std::vector<int>& bs) {
   const int64_t P = n->n_pad;
   const int cap = std::min(kPersistMaxB, l.block);
   int b = l.neurons_per_wg;
@@ -571,8 +572,9 @@ int persist_shape(mc_net* n, const mc_launch& l, int* G, int* B, int* DL, std::v
   const int dl = (int)std::min<size_t>(kPersistMaxWindow, (budget - stat - base) / ((size_t)b * 8));
   const size_t lds = persist_lds_bytes(b, dl);
   HIP_TRY(persist_set_lds_limit(lds));
+  *threads = persist_threads(n, g, l.block, budget - stat - lds);
   int occ = 0;
-  HIP_TRY(persist_occupancy(persist_threads(n, g, l.block, dl), lds, &occ));
+  HIP_TRY(persist_occupancy(*threads, lds, &occ));
   // (workgroups that share a compute unit: two wavefronts per SIMD at most, which fit however they are placed)
   if (occ < 1 || g > n->n_cu * occ || (per_cu > 1 && per_cu * l.block > 512))
     return set_error(MC_ERR_RANGE, "persistent workgroups would not all be co-resident");
@@ -717,7 +719,7 @@ int alloc_persist(mc_net* n, int G, PersistTables* t) {
 int apply_launch(mc_net* n, const mc_launch& l) {
   int rc = validate_launch(n, l);
   if (rc != MC_OK) return rc;
-  int qpw = 0, n_wg = 0, wg_neurons = 0, G = 0, B = 0, DL = 0;
+  int qpw = 0, n_wg = 0, wg_neurons = 0, G = 0, B = 0, DL = 0, pthreads = 0;
   std::vector<int> bs;
   if (l.scheme == MC_SCHEME_STEP_KERNELS || l.scheme == MC_SCHEME_TARGET_OWNER) {
     // step kernels: neurons_per_wg / 4 quads per workgroup; target owner: one
@@ -727,7 +729,7 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     n_wg = (int)((n->n_quads + qpw - 1) / qpw);
     wg_neurons = 4 * qpw;
   } else if (l.scheme == MC_SCHEME_PERSISTENT_LDS) {
-    if ((rc = persist_shape(n, l, &G, &B, &DL, bs)) != MC_OK) return rc;
+    if ((rc = persist_shape(n, l, &G, &B, &DL, &pthreads, bs)) != MC_OK) return rc;
     n_wg = G;
     wg_neurons = B;
   } else {
@@ -746,7 +748,6 @@ int apply_launch(mc_net* n, const mc_launch& l) {
     (void)hipGraphExecDestroy(n->graph);
     n->graph = nullptr;
   }
-  const int pthreads = l.scheme == MC_SCHEME_PERSISTENT_LDS ? persist_threads(n, G, l.block, DL) : 0;
   if (shape_changed || !n->d_raster) {
     // the old shape's buffers go before the new ones are complete: a failure in
     // between leaves no consistent shape, so it marks the handle failed

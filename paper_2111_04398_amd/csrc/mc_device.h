@@ -114,6 +114,7 @@ __host__ __device__ inline size_t window_flag_words(int G) { return window_recor
 constexpr int kPersistMaxB = 512;       // owned targets per workgroup (one per thread)
 constexpr int kPersistMaxBlock = 512;   // threads per workgroup of a launch configuration
 constexpr int kPersistMaxWindow = 102;  // steps of input in LDS (delays up to this - 2 go there: all of them)
+constexpr size_t kPersistLeastLds = 16384;  // LDS that a workgroup of either persistent kernel takes at least (29, 17 KB)
 constexpr int kPersistThreads = 768;   // threads of a workgroup alone on its compute unit: 168 VGPRs per lane
 size_t persist_lds_bytes(int B, int DL);
 // Fills the packed rows and their sub-row bounds for G workgroups of B targets.
