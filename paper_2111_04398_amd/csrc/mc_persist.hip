@@ -67,7 +67,7 @@
 // Bound: latency.  The empty loop of the same exchange takes 1.88 us per step
 // (254 workgroups); a quiet step of the full microcircuit 2.6-3.2 us, a burst
 // about 19 ns per spike.  Mean over 10,000 steps (barriers, three arrays per
-// synapse and a side array of ids -> this form): full microcircuit 9.0 -> 4.0
+// synapse and a side array of ids -> this form): full microcircuit 9.0 -> 3.9
 // us, balanced network 5.0 -> 2.6 us, calls of 20 steps 143-160 -> 86-92 us.
 #pragma clang fp contract(off)
 
